@@ -6,181 +6,114 @@
 //                                    output projection and the MLP's down
 //                                    projection add into the hidden state
 //   SWIGLU  H[m][j] = SiLU(gate) * up (bf16), gate = A W_gate^T,
-//           up = A W_up^T: the tile's 32-column blocks alternate gate and up
-//           rows of the same hidden units, so a lane holds both factors of
-//           each output in matching registers.
+//           up = A W_up^T: the wave's 16-column fragment blocks alternate gate
+//           and up rows of the same hidden units, so a lane holds both factors
+//           of each output in matching registers.
 //
-// Main loop (gfx950): a 256 x 256 tile on 8 waves (two per SIMD), each a
-// 64 x 128 piece on v_mfma_f32_32x32x16_bf16; A and B go global -> LDS by
-// DMA (global_load_lds_dwordx4) into 5 stages of BK = 32, with the 16-byte
-// chunks of each 64-byte row XOR-swizzled by (row >> 2) & 3 so fragment reads
-// are conflict free; one barrier per K-step, the refill of K-step kt + 5
-// interleaved with the MFMAs of K-step kt.  Tiles are dealt to the 8 XCDs in
-// contiguous runs and walked in pairs of M-tiles, N fastest.
-#include "sr_device.hpp"
+// Main loop: the 256 x 256 tile of sr_tile.hpp.  The weight rows of a wave's
+// 128 columns are fed in the order that gives a lane 8 neighbouring columns
+// (RESID) or 4 neighbouring hidden units (SWIGLU), so a row of the residual is
+// two 16-byte accesses per lane and a row of hidden units one of 8 bytes.
+#include "sr_tile.hpp"
 
 #include <type_traits>
 
 namespace sr {
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 32, THREADS = 512, NS = 5;
-constexpr int A_BYTES = BM * 64, B_BYTES = BN * 64, STAGE = A_BYTES + B_BYTES;
-constexpr int LPK = 4;   // DMA instructions per wave per K-step (2 A + 2 B blocks of 1 KB)
-
-typedef __attribute__((address_space(3))) char lchar;
-typedef unsigned int nu32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint4 ld16(const lchar* p) {
-  return __builtin_bit_cast(uint4, *reinterpret_cast<const __attribute__((address_space(3))) nu32x4*>(p));
-}
-__device__ __forceinline__ int swz(int r) { return (r >> 2) & 3; }
-
-__device__ __forceinline__ void tile_of(int b, int tm, int tn, int& mt, int& nt) {
-  const int nb = tm * tn;
-  const int per = nb / 8, rem = nb % 8;
-  const int x = b % 8, loc = b / 8;
-  const int t = x * per + (x < rem ? x : rem) + loc;
-  constexpr int GM = 2;
-  const int grp = t / (GM * tn);
-  const int first = grp * GM;
-  const int gs = (tm - first) < GM ? (tm - first) : GM;
-  const int idx = t - grp * GM * tn;
-  mt = first + idx % gs;
-  nt = idx / gs;
-}
-
 __device__ __forceinline__ float silu(float x) { return x * __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
 
 template <int MODE>
-__global__ __launch_bounds__(THREADS, 1) void block_gemm_kernel(BlockGemmArgs a, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(kTileThreads, 1) void block_gemm_kernel(BlockGemmArgs a, int tiles_m, int tiles_n) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
-  __shared__ __attribute__((aligned(1024))) char smem_raw[NS * STAGE];
-  lchar* smem = (lchar*)smem_raw;
+  __shared__ __attribute__((aligned(1024))) char smem[kTileLds];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wid >> 1, wn = wid & 1;
-  const int lc = lane & 31, fhi = lane >> 5;
+  const int lc = lane & 15, g = lane >> 4;
   int mt, nt;
   tile_of(blockIdx.x, tiles_m, tiles_n, mt, nt);
-  const int64_t row0 = (int64_t)mt * BM;
-  const int n0 = nt * BN;
+  const int64_t row0 = (int64_t)mt * kTileM;
+  const int n0 = nt * kTileN;
   const int K = a.K;
   const int64_t M = a.M;
 
-  // DMA sources: wave wid fills A and B blocks 2 wid, 2 wid + 1 (16 rows each)
-  const char* a_src[2];
-  const char* b_src[2];
+  const char* a_base = static_cast<const char*>(a.A) + row0 * K * 2;
+  uint32_t a_off[8];
+  const char* b_ptr[TileB<bf16_t>::DMAS];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int row = (wid * 2 + i) * 16 + (lane >> 2);
-    const int c = (lane & 3) ^ swz(row);
-    int64_t mr = row0 + row;
-    mr = mr >= M ? M - 1 : mr;          // rows past M are never stored
-    a_src[i] = static_cast<const char*>(a.A) + (mr * K + c * 8) * 2;
-    const int n = n0 + row;
+  for (int i = 0; i < 8; ++i) {
+    int row = tile_a_row(wid, i, lane);
+    const int chunk = tile_a_chunk(row, lane);
+    const int64_t last = M - 1 - row0;             // rows past M are never stored
+    row = row < last ? row : (int)last;
+    a_off[i] = (uint32_t)(row * (K * 2) + chunk * 16);
+  }
+#pragma unroll
+  for (int i = 0; i < TileB<bf16_t>::DMAS; ++i) {
+    const int row = tile_b_row<bf16_t>(wid, i, lane);
+    const int h = row >> 7, j = (row >> 4) & 7, c = row & 15;   // column half, fragment block, lane
     const char* w;
     int64_t wr;
     if constexpr (MODE == kGemmSwiglu) {
-      const int blk = row >> 5;          // 32-row blocks alternate gate / up
-      wr = (int64_t)nt * 128 + (blk >> 1) * 32 + (row & 31);
-      w = static_cast<const char*>((blk & 1) ? a.B2 : a.B);
+      w = static_cast<const char*>((j & 1) ? a.B2 : a.B);
+      wr = (int64_t)nt * 128 + h * 64 + 4 * c + (j >> 1);
     } else {
-      wr = n;
       w = static_cast<const char*>(a.B);
+      wr = n0 + h * 128 + 8 * c + j;
     }
-    b_src[i] = w + (wr * K + c * 8) * 2;
+    b_ptr[i] = w + wr * K * 2 + tile_b_chunk<bf16_t>(row, lane) * 16;
   }
-  const int arow = wm * 64 + lc;
-  const int brow = wn * 128 + lc;
-  const int a_k0 = arow * 64 + ((0 + fhi) ^ swz(arow)) * 16;
-  const int a_k1 = arow * 64 + ((2 + fhi) ^ swz(arow)) * 16;
-  const int b_k0 = A_BYTES + brow * 64 + ((0 + fhi) ^ swz(brow)) * 16;
-  const int b_k1 = A_BYTES + brow * 64 + ((2 + fhi) ^ swz(brow)) * 16;
+  f32x4 acc[8][8];
+  tile_zero(acc);
+  tile_main_loop<bf16_t, 8>(acc, a_base, a_off, b_ptr, K / kTileK, smem, wid, lane);
 
-  bf16x8 fa[2][2], fb[2][4];
-  f32x16 acc[2][4];
+  // ---- epilogue: acc[i][j][r] is tile row 128 wm + 32 g + 4 i + r of the
+  // lane's block j
+  const int64_t lrow = row0 + wm * 128 + 32 * g;
+  if constexpr (MODE == kGemmSwiglu) {
+    uint16_t* out = static_cast<uint16_t*>(a.C) + lrow * a.ldc + (int64_t)nt * 128 + wn * 64 + 4 * lc;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 8; ++i) {
+      f32x4 x[8];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = zero16();
-
-  // fragment q of a K-step: 0, 1 A (rows +0, +32 of the wave's band), 2..5 B
-  auto read_one = [&](int stage, int ks, int slot, int qq) {
-    const int q = qq == 0 ? 0 : (qq <= 4 ? qq + 1 : 1);   // order A0, B0..B3, A1
-    const lchar* sb = smem + stage * STAGE;
-    if (q < 2) fa[slot][q] = as_bf16x8(ld16(sb + (ks ? a_k1 : a_k0) + q * 32 * 64));
-    else fb[slot][q - 2] = as_bf16x8(ld16(sb + (ks ? b_k1 : b_k0) + (q - 2) * 32 * 64));
-  };
-  auto mma_one = [&](int slot, int q) {
-    const int i = q >> 2, j = q & 3;
-    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[slot][i], fb[slot][j], acc[i][j], 0, 0, 0);
-  };
-  auto dma_one = [&](int kt, int stage, int q) {
-    const uint32_t lds0 = (uint32_t)(uintptr_t)smem + stage * STAGE;
-    if (q < 2) dma16(a_src[q] + (int64_t)kt * BK * 2, lds0 + (wid * 2 + q) * 1024);
-    else dma16(b_src[q - 2] + (int64_t)kt * BK * 2, lds0 + A_BYTES + (wid * 2 + q - 2) * 1024);
-  };
-
-  const int KT = K / BK;
+      for (int j = 0; j < 8; ++j) x[j] = tile_take(acc[i][j]);
 #pragma unroll
-  for (int s = 0; s < NS; ++s)
-#pragma unroll
-    for (int q = 0; q < LPK; ++q) dma_one(s < KT ? s : KT - 1, s, q);
-  wait_vm<(NS - 1) * LPK>();
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_sched_barrier(0);
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int q = 0; q < 6; ++q) read_one(0, 0, 0, q);
-
-  int st = 0;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int st1 = st + 1 == NS ? 0 : st + 1;
-    const int kn = kt + NS < KT ? kt + NS : KT - 1;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      mma_one(0, q);
-      if (q < 6) read_one(st, 1, 1, q);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int r = 0; r < 4; ++r) {
+        uint2 v;
+        v.x = pack_bf16x2(silu(x[0][r]) * x[1][r], silu(x[2][r]) * x[3][r]);
+        v.y = pack_bf16x2(silu(x[4][r]) * x[5][r], silu(x[6][r]) * x[7][r]);
+        if (lrow + 4 * i + r < M) *reinterpret_cast<uint2*>(out + (4 * i + r) * a.ldc) = v;
+      }
     }
-    // this wave's reads of stage st are done and K-step kt + 1 has landed;
-    // after the barrier stage st may be refilled and stage st1 read
-    wait_vm<(NS - 2) * LPK>();
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
+  } else {
+    // 16 rows of the residual are read before the first of them is written:
+    // read one by one, every row would wait for memory
+    float* out = static_cast<float*>(a.C) + lrow * a.ldc + n0 + wn * 128 + 8 * lc;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      mma_one(1, q);
-      if (q < 6) read_one(st1, 0, 0, q);
-      if ((q & 1) == 0) dma_one(kn, st, q >> 1);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    st = st1;
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  wait_vm<0>();                          // no DMA may still be landing in LDS
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  __builtin_amdgcn_s_barrier();
-
-  // ---- epilogue: acc[i][j] register r of lane l is tile row
-  // 64 wm + 32 i + acc_row(r, l), column 128 wn + 32 j + l % 32
+    for (int h = 0; h < 2; ++h) {
+      f32x4 res[16][2];
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+      for (int u = 0; u < 16; ++u) {
+        const int64_t at = (lrow + 16 * h + u < M ? 16 * h + u : 0) * a.ldc;   // row lrow stands in past M
+        const f32x4* p = reinterpret_cast<const f32x4*>(lrow < M ? out + at : static_cast<const float*>(a.C));
+        res[u][0] = p[0];
+        res[u][1] = p[1];
+      }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int64_t row = row0 + wm * 64 + 32 * i + acc_row(r, lane);
-      if (row >= M) continue;
-      if constexpr (MODE == kGemmSwiglu) {
-        uint16_t* out = static_cast<uint16_t*>(a.C) + row * a.ldc + (int64_t)nt * 128 + wn * 64 + lc;
-        out[0] = f32_to_bf16_bits(silu(acc[i][0][r]) * acc[i][1][r]);
-        out[32] = f32_to_bf16_bits(silu(acc[i][2][r]) * acc[i][3][r]);
-      } else {
-        float* out = static_cast<float*>(a.C) + row * a.ldc + n0 + wn * 128 + lc;
+      for (int q = 0; q < 4; ++q) {
+        f32x4 x[8];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) out[32 * j] += acc[i][j][r];
+        for (int j = 0; j < 8; ++j) x[j] = tile_take(acc[4 * h + q][j]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int u = 4 * q + r;
+          f32x4* p = reinterpret_cast<f32x4*>(out + (16 * h + u) * a.ldc);
+          if (lrow + 16 * h + u < M) {
+            p[0] = res[u][0] + f32x4{x[0][r], x[1][r], x[2][r], x[3][r]};
+            p[1] = res[u][1] + f32x4{x[4][r], x[5][r], x[6][r], x[7][r]};
+          }
+        }
       }
     }
   }
@@ -189,9 +122,9 @@ __global__ __launch_bounds__(THREADS, 1) void block_gemm_kernel(BlockGemmArgs a,
 template <int MODE>
 hipError_t run_gemm(const BlockGemmArgs& a, hipStream_t s) {
   if (a.M == 0) return hipSuccess;
-  if (a.K % BK || a.N % BN) return hipErrorInvalidValue;
-  const int tm = (int)((a.M + BM - 1) / BM), tn = a.N / BN;
-  hipLaunchKernelGGL((block_gemm_kernel<MODE>), dim3(tm * tn), dim3(THREADS), 0, s, a, tm, tn);
+  if (a.K < kTileK || a.K % kTileK || a.N % kTileN) return hipErrorInvalidValue;
+  const int tm = (int)((a.M + kTileM - 1) / kTileM), tn = a.N / kTileN;
+  hipLaunchKernelGGL((block_gemm_kernel<MODE>), dim3(tm * tn), dim3(kTileThreads), 0, s, a, tm, tn);
   return hipGetLastError();
 }
 
