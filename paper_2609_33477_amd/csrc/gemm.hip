@@ -11,9 +11,10 @@
 //           of each output in matching registers.
 //
 // Main loop: the 256 x 256 tile of sr_tile.hpp.  The weight rows of a wave's
-// 128 columns are fed in the order that gives a lane 8 neighbouring columns
-// (RESID) or 4 neighbouring hidden units (SWIGLU), so a row of the residual is
-// two 16-byte accesses per lane and a row of hidden units one of 8 bytes.
+// 128 columns are fed in the order that gives a lane 4 neighbouring columns of
+// each 64 (RESID) or 4 neighbouring hidden units (SWIGLU), so the residual is
+// accessed 16 bytes per lane (256 contiguous bytes per row) and hidden units
+// are stored 8 bytes per lane.
 #include "sr_tile.hpp"
 
 #include <type_traits>
@@ -39,10 +40,10 @@ __global__ __launch_bounds__(kTileThreads, 1) void block_gemm_kernel(BlockGemmAr
   const int64_t M = a.M;
 
   const char* a_base = static_cast<const char*>(a.A) + row0 * K * 2;
-  uint32_t a_off[8];
+  uint32_t a_off[4];
   const char* b_ptr[TileB<bf16_t>::DMAS];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < 4; ++i) {
     int row = tile_a_row(wid, i, lane);
     const int chunk = tile_a_chunk(row, lane);
     const int64_t last = M - 1 - row0;             // rows past M are never stored
@@ -60,21 +61,21 @@ __global__ __launch_bounds__(kTileThreads, 1) void block_gemm_kernel(BlockGemmAr
       wr = (int64_t)nt * 128 + h * 64 + 4 * c + (j >> 1);
     } else {
       w = static_cast<const char*>(a.B);
-      wr = n0 + h * 128 + 8 * c + j;
+      wr = n0 + h * 128 + 64 * (j >> 2) + 4 * c + (j & 3);
     }
     b_ptr[i] = w + wr * K * 2 + tile_b_chunk<bf16_t>(row, lane) * 16;
   }
-  f32x4 acc[8][8];
+  f32x4 acc[4][8];
   tile_zero(acc);
   tile_main_loop<bf16_t, 8>(acc, a_base, a_off, b_ptr, K / kTileK, smem, wid, lane);
 
-  // ---- epilogue: acc[i][j][r] is tile row 128 wm + 32 g + 4 i + r of the
+  // ---- epilogue: acc[i][j][r] is tile row 64 wm + 16 g + 4 i + r of the
   // lane's block j
-  const int64_t lrow = row0 + wm * 128 + 32 * g;
+  const int64_t lrow = row0 + wm * 64 + 16 * g;
   if constexpr (MODE == kGemmSwiglu) {
     uint16_t* out = static_cast<uint16_t*>(a.C) + lrow * a.ldc + (int64_t)nt * 128 + wn * 64 + 4 * lc;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 4; ++i) {
       f32x4 x[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) x[j] = tile_take(acc[i][j]);
@@ -87,31 +88,31 @@ __global__ __launch_bounds__(kTileThreads, 1) void block_gemm_kernel(BlockGemmAr
       }
     }
   } else {
-    // 16 rows of the residual are read before the first of them is written:
+    // 8 rows of the residual are read before the first of them is written:
     // read one by one, every row would wait for memory
-    float* out = static_cast<float*>(a.C) + lrow * a.ldc + n0 + wn * 128 + 8 * lc;
+    float* out = static_cast<float*>(a.C) + lrow * a.ldc + n0 + wn * 128 + 4 * lc;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-      f32x4 res[16][2];
+      f32x4 res[8][2];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) {
-        const int64_t at = (lrow + 16 * h + u < M ? 16 * h + u : 0) * a.ldc;   // row lrow stands in past M
-        const f32x4* p = reinterpret_cast<const f32x4*>(lrow < M ? out + at : static_cast<const float*>(a.C));
-        res[u][0] = p[0];
-        res[u][1] = p[1];
+      for (int u = 0; u < 8; ++u) {
+        const bool ok = lrow + 8 * h + u < M;       // past M the first row of C stands in
+        const float* p = ok ? out + (8 * h + u) * a.ldc : static_cast<const float*>(a.C);
+        res[u][0] = *reinterpret_cast<const f32x4*>(p);
+        res[u][1] = *reinterpret_cast<const f32x4*>(p + 64);
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < 2; ++q) {
         f32x4 x[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = tile_take(acc[4 * h + q][j]);
+        for (int j = 0; j < 8; ++j) x[j] = tile_take(acc[2 * h + q][j]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const int u = 4 * q + r;
-          f32x4* p = reinterpret_cast<f32x4*>(out + (16 * h + u) * a.ldc);
-          if (lrow + 16 * h + u < M) {
-            p[0] = res[u][0] + f32x4{x[0][r], x[1][r], x[2][r], x[3][r]};
-            p[1] = res[u][1] + f32x4{x[4][r], x[5][r], x[6][r], x[7][r]};
+          float* p = out + (8 * h + u) * a.ldc;
+          if (lrow + 8 * h + u < M) {
+            *reinterpret_cast<f32x4*>(p) = res[u][0] + f32x4{x[0][r], x[1][r], x[2][r], x[3][r]};
+            *reinterpret_cast<f32x4*>(p + 64) = res[u][1] + f32x4{x[4][r], x[5][r], x[6][r], x[7][r]};
           }
         }
       }

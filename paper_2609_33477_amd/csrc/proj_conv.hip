@@ -14,7 +14,7 @@
 // registers and only k_hat / v (bf16, head-major [H][T][d]), G and beta ([H_v][T],
 // fp32) and the tail rows are written.
 //
-// Main loop: the 256 x 256 tile of sr_tile.hpp (4 waves of 128 x 128 on
+// Main loop: the 256 x 256 tile of sr_tile.hpp (8 waves of 64 x 128 on
 // v_mfma_f32_16x16x32_bf16, K-steps of 64 through the LDS by DMA).  fp8 (E4M3)
 // weights are staged as bytes and converted to bf16 after the fragment read
 // (exact); the per-channel scale is folded into the conv taps (the conv is
@@ -35,18 +35,18 @@
 // Conv epilogue, in registers: M-tiles overlap by 3 rows (stride 253), so
 // every output row's w-1 predecessors are in the tile (the first tile starts
 // at row 0 and outputs all of its rows).  Lane l of wave w holds rows
-// 128 (w / 2) + 32 (l / 16) + 0..31 of 8 columns; the conv runs down those
+// 64 (w / 2) + 16 (l / 16) + 0..15 of 8 columns; the conv runs down those
 // registers (the 3 rows above the lane's first come from the lane before it
 // through a small LDS exchange), then SiLU.  The weight rows of a head are fed
-// in the order that gives a lane D / 16 neighbouring columns of it, so a row of
-// a 128-wide head leaves as one 16-byte store per lane (256 contiguous bytes
-// per row) and its taps arrive the same way.  A key's sum of squares is
-// summed over the lane's columns and then across its 16 lanes by a DPP
-// reduce-scatter; the inverse norms go back through the LDS.  Values need no
-// norm and are stored as the conv produces them.  Waves with a row near a
+// in the order that gives a lane 4 neighbouring columns of each 64 (2 of a
+// 32-wide head), so 64 columns of a row leave as one 8-byte store per lane
+// (128 contiguous bytes) and their taps arrive the same way.  A key's sum of
+// squares is summed over the lane's columns and then across its 16 lanes by a
+// DPP reduce-scatter; the inverse norms go back through the LDS.  Values need
+// no norm and are stored as the conv produces them.  Waves with a row near a
 // segment start or end (the conv tail) or past T take masked variants.  The
-// segment info and conv taps the epilogue needs are loaded before the main
-// loop.
+// segment info and conv taps are loaded when the main loop ends: held across
+// it they would not fit beside the fragments in a wave's 128 VGPRs.
 //
 // Gate columns (no conv) keep their natural order and leave through a per-wave
 // LDS transpose, so their head-major G and beta planes get stores of 64
@@ -73,10 +73,10 @@ namespace {
 constexpr int HALO = 3, SM = kTileM - HALO;       // tile row stride
 // Epilogue areas in the drained stages: the last 3 rows of each lane's 8
 // columns, the inverse norms of each group's rows (up to 4 heads per wave),
-// and per wave a 16-column block of gate values, 128 rows per column.
+// and per wave a 16-column block of gate values, 64 rows per column.
 constexpr int XB_BYTES = kTileThreads * 24 * 4;
-constexpr int INV_BYTES = kTileWaves * 4 * 4 * 32 * 4;
-constexpr int GATE_OFF = XB_BYTES + INV_BYTES, GATE_WAVE = 16 * 128 * 4;
+constexpr int INV_BYTES = kTileWaves * 4 * 4 * 16 * 4;
+constexpr int GATE_OFF = XB_BYTES + INV_BYTES, GATE_WAVE = 16 * 64 * 4;
 static_assert(GATE_OFF + kTileWaves * GATE_WAVE <= kTileLds, "epilogue areas");
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
@@ -162,11 +162,10 @@ __device__ __forceinline__ float fast_sigmoid(float x) { return __builtin_amdgcn
 // 6e-8 in a value that then scales a log-decay
 __device__ __forceinline__ float softplus(float x) { return fmaxf(x, 0.f) + __logf(1.f + __expf(-fabsf(x))); }
 
-// N neighbouring bf16 (N = 2, 4, 8) as one store
+// N neighbouring bf16 (N = 2, 4) as one store
 template <int N>
 __device__ __forceinline__ void store_bf16(uint16_t* p, const uint32_t* v) {
-  if constexpr (N == 8) *reinterpret_cast<uint4*>(p) = uint4{v[0], v[1], v[2], v[3]};
-  else if constexpr (N == 4) *reinterpret_cast<uint2*>(p) = uint2{v[0], v[1]};
+  if constexpr (N == 4) *reinterpret_cast<uint2*>(p) = uint2{v[0], v[1]};
   else *reinterpret_cast<uint32_t*>(p) = v[0];
 }
 
@@ -195,7 +194,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
-  const int wm = wid >> 1, wn = wid & 1;                       // 128-row x 128-column sub-tile
+  const int wm = wid >> 1, wn = wid & 1;                       // 64-row x 128-column sub-tile
   const int g = lane >> 4, lc = lane & 15;
   // m-tiles of the layers stacked: the XCD-aware walk runs over all of them
   int mt, nt;
@@ -209,22 +208,54 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
   const int K = a.K;
   const int64_t T = a.T;
 
-  // Output columns: JB = D / 16 neighbouring columns of each of the wave's NH
-  // heads per lane; past the conv and z columns (the gates) 16-column blocks
-  // in natural order.  Fragment block j, lane c of column half h:
-  constexpr int NH = 128 / D, JB = D / 16;
-  auto head0 = [&](int h, int j) { return n0 + 128 * h + (j / JB) * D; };   // first column of the block's head
+  // Output columns.  The wave's 128 are NG groups of GW (64, or a 32-wide
+  // head); of a conv or z group a lane holds JG neighbouring columns, past
+  // them (the gates) 16-column blocks in natural order.  Fragment block j,
+  // lane c of column half h:
+  constexpr int NH = 128 / D, JG = D >= 64 ? 4 : 2, GW = 16 * JG, GH = D / GW;
+  auto group0 = [&](int h, int j) { return n0 + 128 * h + (j / JG) * GW; };   // first column of the block's group
   auto column = [&](int h, int j, int c) {
-    const int nb = head0(h, j);
-    return nb < a.C_z ? nb + JB * c + j % JB : nb + 16 * (j % JB) + c;
+    const int nb = group0(h, j);
+    return nb < a.C_z ? nb + JG * c + j % JG : nb + 16 * (j % JG) + c;
   };
 
-  // The epilogue share of this lane: tile rows rbase .. rbase + 31 of columns
-  // column(wn, j, lc).  Its inputs are fetched before the first DMA so their
-  // latency hides under the main loop (and no wait_vm count below has to
-  // include them): the segment position and rows left of the first row, the
-  // raw conv taps of the columns and their fp8 scales.
-  const int rbase = wm * 128 + 32 * g;
+  // ------------------------------------------------------------ main loop
+  f32x4 acc[4][8];
+  tile_zero(acc);
+  {
+    const char* a_base = static_cast<const char*>(a.A) + row0 * K * 2;
+    uint32_t a_off[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = tile_a_row(wid, i, lane);
+      const int64_t last = T - 1 - row0;             // rows past T are never output
+      a_off[i] = (uint32_t)((row < last ? row : (int)last) * (K * 2) + tile_a_chunk(row, lane) * 16);
+    }
+    const char* b_ptr[TileB<TB>::DMAS];
+#pragma unroll
+    for (int i = 0; i < TileB<TB>::DMAS; ++i) {
+      const int row = tile_b_row<TB>(wid, i, lane);
+      const int n_out = column(row >> 7, (row >> 4) & 7, row & 15);
+      const int n = real_col<RECT, D>(a, n_out < a.N ? n_out : a.N - 1);
+      const char* p = static_cast<const char*>(a.seg[0].ptr);
+#pragma unroll
+      for (int s = 0; s < 6; ++s)
+        if (s < a.n_wseg && n >= a.seg[s].n0 && n < a.seg[s].n1)
+          p = static_cast<const char*>(a.seg[s].ptr) + (int64_t)(n - a.seg[s].n0) * K * Elem<TB>::bytes;
+      b_ptr[i] = p + tile_b_chunk<TB>(row, lane) * 16;
+    }
+    const int n_wave = a.N - (n0 + wn * 128);        // valid columns of this wave's 128
+    const int KT = K / kTileK;
+    if (n_wave > 64) tile_main_loop<TB, 8>(acc, a_base, a_off, b_ptr, KT, smem_raw, wid, lane);
+    else if (n_wave > 0) tile_main_loop<TB, 4>(acc, a_base, a_off, b_ptr, KT, smem_raw, wid, lane);
+    else tile_main_loop<TB, 0>(acc, a_base, a_off, b_ptr, KT, smem_raw, wid, lane);
+  }
+
+  // ------------------------------------------------------------ epilogue
+  // The share of this lane: tile rows rbase .. rbase + 15 of columns
+  // column(wn, j, lc).  Its inputs: the segment position and rows left of the
+  // first row, the raw conv taps of the columns and their fp8 scales.
+  const int rbase = wm * 64 + 16 * g;
   const int64_t t0 = row0 + rbase;
   int pos0 = -1, rem0 = 0;
   if (t0 < T) {
@@ -234,102 +265,26 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
   }
   // RECT: a key head's pad columns (from k_real on) hold products of a
   // repeated weight row; they enter neither the conv outputs, the tail, nor
-  // the key's norm.  k_real is a multiple of JB: a lane is all pad or none.
-  const bool pad_lane = RECT && n0 + 128 * wn < a.C_k && JB * lc >= a.k_real;
-  // Raw conv taps, decoded in the epilogue (touching them here would make the
-  // prologue wait for the loads): with w = 4 and an aligned table, 8 (bf16)
-  // or 16 (fp32) bytes per column, [row t-3, t-2, t-1, t], the lane's JB
-  // columns of a head neighbouring; else one element per tap, tr[j][d]
-  // holding the tap of row t - d.
+  // the key's norm.  k_real is a multiple of JG: a lane's group is all pad or
+  // none.
+  const bool rect_k = RECT && n0 + 128 * wn < a.C_k;
+  auto pad_lane = [&](int q) { return rect_k && GW * (q % GH) + JG * lc >= a.k_real; };
+  // With w = 4 and an aligned table a column's conv taps, [row t-3, t-2, t-1,
+  // t], are 8 (bf16) or 16 (fp32) bytes and the lane's JG columns of a group
+  // neighbours; else they are read one by one.
   const int tap_mode = (a.w == 4 && (reinterpret_cast<uintptr_t>(a.conv_w) & 15) == 0) ? (a.conv_bf16 ? 1 : 2) : 0;
-  uint32_t tr[8][4], sc_raw[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    sc_raw[j] = 0x3f80u;   // bf16 bits of 1
-#pragma unroll
-    for (int d = 0; d < 4; ++d) tr[j][d] = 0u;
-  }
-  static_for<NH>([&](auto hd_c) {
-    constexpr int hd = decltype(hd_c)::value, j0 = hd * JB;
-    const int nb = head0(wn, j0);
+  // fp8 scale (bf16 bits) of fragment block j's column
+  auto scale = [&](int j) {
+    uint32_t bits = 0x3f80u;   // 1
     if constexpr (FP8) {
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj) {
-        const int n_out = column(wn, j0 + jj, lc);
-        if (n_out < a.N) sc_raw[j0 + jj] = *col_scale_ptr(a, real_col<RECT, D>(a, n_out));
-      }
+      const int n = column(wn, j, lc);
+      bits = *col_scale_ptr(a, real_col<RECT, D>(a, n < a.N ? n : a.N - 1));
     }
-    if (nb < a.C_kv) {
-      // first channel of the lane's JB (a pad lane: the head's last JB)
-      const int ch0 = pad_lane ? real_col<RECT, D>(a, nb) + a.k_real - JB : real_col<RECT, D>(a, nb + JB * lc);
-      if (tap_mode == 1) {
-        const uint4* p = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.conv_w) + (int64_t)ch0 * 4);
-#pragma unroll
-        for (int jj = 0; jj < JB; jj += 2) {
-          const uint4 v = p[jj / 2];
-          tr[j0 + jj][0] = v.x;
-          tr[j0 + jj][1] = v.y;
-          tr[j0 + jj + 1][0] = v.z;
-          tr[j0 + jj + 1][1] = v.w;
-        }
-      } else if (tap_mode == 2) {
-        const uint4* p = reinterpret_cast<const uint4*>(static_cast<const float*>(a.conv_w) + (int64_t)ch0 * 4);
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj) {
-          const uint4 v = p[jj];
-          tr[j0 + jj][0] = v.x;
-          tr[j0 + jj][1] = v.y;
-          tr[j0 + jj][2] = v.z;
-          tr[j0 + jj][3] = v.w;
-        }
-      } else {
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj)
-#pragma unroll
-          for (int d = 0; d < 4; ++d) {
-            if (d < a.w) {
-              const int64_t i = (int64_t)(ch0 + jj) * a.w + a.w - 1 - d;   // tap of row t - d
-              tr[j0 + jj][d] = a.conv_bf16 ? (uint32_t) static_cast<const uint16_t*>(a.conv_w)[i]
-                                           : static_cast<const uint32_t*>(a.conv_w)[i];
-            }
-          }
-      }
-    }
-  });
-
-  // ------------------------------------------------------------ main loop
-  const char* a_base = static_cast<const char*>(a.A) + row0 * K * 2;
-  uint32_t a_off[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int row = tile_a_row(wid, i, lane);
-    const int64_t last = T - 1 - row0;             // rows past T are never output
-    a_off[i] = (uint32_t)((row < last ? row : (int)last) * (K * 2) + tile_a_chunk(row, lane) * 16);
-  }
-  const char* b_ptr[TileB<TB>::DMAS];
-#pragma unroll
-  for (int i = 0; i < TileB<TB>::DMAS; ++i) {
-    const int row = tile_b_row<TB>(wid, i, lane);
-    const int n_out = column(row >> 7, (row >> 4) & 7, row & 15);
-    const int n = real_col<RECT, D>(a, n_out < a.N ? n_out : a.N - 1);
-    const char* p = static_cast<const char*>(a.seg[0].ptr);
-#pragma unroll
-    for (int s = 0; s < 6; ++s)
-      if (s < a.n_wseg && n >= a.seg[s].n0 && n < a.seg[s].n1)
-        p = static_cast<const char*>(a.seg[s].ptr) + (int64_t)(n - a.seg[s].n0) * K * Elem<TB>::bytes;
-    b_ptr[i] = p + tile_b_chunk<TB>(row, lane) * 16;
-  }
-  f32x4 acc[8][8];
-  tile_zero(acc);
-  const int n_wave = a.N - (n0 + wn * 128);        // valid columns of this wave's 128
-  const int KT = K / kTileK;
-  if (n_wave > 64) tile_main_loop<TB, 8>(acc, a_base, a_off, b_ptr, KT, smem_raw, wid, lane);
-  else if (n_wave > 0) tile_main_loop<TB, 4>(acc, a_base, a_off, b_ptr, KT, smem_raw, wid, lane);
-  else tile_main_loop<TB, 0>(acc, a_base, a_off, b_ptr, KT, smem_raw, wid, lane);
+    return bf16_bits_to_f32(bits);
+  };
   tile_drain();
   tile_pin(acc);
 
-  // ------------------------------------------------------------ epilogue
   // acc[i][j][r]: the raw projection of row rbase + 4 i + r, fragment block j.
   // The conv runs down a lane's registers; only the 3 rows before rbase come
   // from another lane (16 lanes down in this wave, or the last group of the
@@ -340,7 +295,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
     lfloat* p = XB + (wid * 64 + lane) * 24;
     f32x4 x[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = tile_take(acc[7][j]);
+    for (int j = 0; j < 8; ++j) x[j] = tile_take(acc[3][j]);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       st_f4(p + 8 * k, x[0][1 + k], x[1][1 + k], x[2][1 + k], x[3][1 + k]);
@@ -349,26 +304,15 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
   }
   __builtin_amdgcn_s_waitcnt(0xc07f);
   __builtin_amdgcn_s_barrier();
-  float xp[3][8];    // xp[k][j]: row rbase - 3 + k of block j (zero above the tile)
-  {
-    const int src = g ? wid * 64 + lane - 16 : (wm ? (wid - 2) * 64 + lane + 48 : lane);
-    const lfloat* p = XB + src * 24;
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const nf32x4 v = *reinterpret_cast<const __attribute__((address_space(3))) nf32x4*>(p + 8 * k + 4 * h);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) xp[k][4 * h + e] = rbase == 0 ? 0.f : v[e];
-      }
-  }
+  // rows rbase - 3 .. - 1 of the lane's columns, [3][8] (unused above the tile)
+  const lfloat* above = XB + (g ? wid * 64 + lane - 16 : (wm ? (wid - 2) * 64 + lane + 48 : lane)) * 24;
 
   const int w1 = a.w - 1;
-  // Fast case: all 32 rows lie inside one segment, at least w - 1 rows past
+  // Fast case: all 16 rows lie inside one segment, at least w - 1 rows past
   // its start (or the first of them are halo rows) and more than w - 1 rows
   // before its end (no tail rows).  Otherwise the masks are built from the
   // rows' segment info.
-  const bool fast = rem0 >= 32 + w1 && (pos0 >= w1 || (rbase == 0 && hal));
+  const bool fast = rem0 >= 16 + w1 && (pos0 >= w1 || (rbase == 0 && hal));
   const bool wave_fast = __builtin_amdgcn_ballot_w64(!fast) == 0;
   // bit u of m1 / m2 / m3: row u may use row u-1 / u-2 / u-3 (same segment);
   // outm: row u is an output; tailm: row u is one of its segment's last w-1
@@ -377,7 +321,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
   if (!wave_fast && !fast) {
     m1 = m2 = m3 = outm = 0u;
 #pragma unroll
-    for (int b = 0; b < 4; ++b) {
+    for (int b = 0; b < 2; ++b) {
       int2 pr[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -403,218 +347,281 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
   const bool tail_bf16 = a.tail_bf16 != 0;
   const uint32_t tail_rows = wave_fast ? 0u : wave_reduce<true>(tailm);   // rows some lane keeps for the tail
 
-  // conv taps (row t - d) with the fp8 column scale and -log2(e) folded in:
-  // the conv yields z = -log2(e) c, so e^-c = 2^z and
-  // SiLU(c) = z / (-log2(e) (1 + 2^z))
-  float tp[8][4];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-      uint32_t bits;
-      if (tap_mode == 1) bits = (d & 1) ? tr[j][(3 - d) >> 1] << 16 : tr[j][(3 - d) >> 1] & 0xffff0000u;
-      else if (tap_mode == 2) bits = tr[j][3 - d];
-      else bits = a.conv_bf16 ? tr[j][d] << 16 : tr[j][d];
-      tp[j][d] = __builtin_bit_cast(float, bits) * bf16_bits_to_f32(sc_raw[j]) * -kLog2e;
-    }
-  }
-
   static_for<NH>([&](auto hd_c) {
-    constexpr int hd = decltype(hd_c)::value, j0 = hd * JB;
-    const int nb = head0(wn, j0);            // first column of the head (wave-uniform)
+    constexpr int hd = decltype(hd_c)::value;
+    const int nb = n0 + 128 * wn + hd * D;   // first column of the head (wave-uniform)
     if (nb >= a.N) {
     } else if (nb < a.C_kv) {
       // ---- q, k or v head: conv, SiLU, (queries and keys) L2 norm
       const bool is_q = nb < a.C_q;
       const bool is_k = nb < a.C_k;   // q or k: normalised
-      if (tail_rows) {
-        // the raw projection of the segment's last w-1 rows is the conv state
-        const int ch0 = pad_lane ? 0 : real_col<RECT, D>(a, nb + JB * lc);
+      // destinations of the lane's JG columns of each group, row rbase
+      const int hh = is_q ? nb / D : (is_k ? (nb - a.C_q) / D : (nb - a.C_k) / D);
+      uint16_t* const head = static_cast<uint16_t*>(is_q ? a.Qbuf : (is_k ? a.Kbuf : a.Vbuf)) + ((int64_t)hh * T + t0) * D;
+      uint16_t* dst[GH];
+      bool vpad[GH];
 #pragma unroll
-        for (int u = 0; u < 32; ++u) {
-          if ((tail_rows >> u) & 1u) {
-            if (((tailm >> u) & 1u) && !pad_lane) {
-              const RowInfo r = a.info[t0 + u];
-              if (r.slot >= 0) {
-                const int64_t at = ((int64_t)r.slot * a.c_tail + a.tail_kv_off + ch0) * w1 + (w1 - r.rem);
-                float v[JB];
+      for (int gi = 0; gi < GH; ++gi) {
+        dst[gi] = head + GW * gi + JG * lc;
+        vpad[gi] = false;
+        // RECT values: value head h (v_head = 2 k_real columns) is stored as
+        // two halves 2 h + e of k_real columns, each padded to D like a key
+        // head ([2 H_v][T][D]); the lanes of a half's last D - k_real columns
+        // also write its pad columns (zeros).
+        if (RECT && !is_k) {
+          const int c = nb + GW * gi - a.C_k + JG * lc, h = c / a.v_head, c0 = c - h * a.v_head;
+          const int e = c0 / a.k_real, col = c0 - e * a.k_real;
+          dst[gi] = static_cast<uint16_t*>(a.Vbuf) + ((int64_t)(2 * h + e) * T + t0) * D + col;
+          vpad[gi] = col + (D - a.k_real) >= a.k_real;
+        }
+      }
+      auto put = [&](int gi, int u, const uint32_t* v) { store_bf16<JG>(dst[gi] + u * D, v); };
+      // store of row u.  SIMPLE: only the tile's first rows may not be output
+      auto row_out = [&](int gi, int u, const uint32_t* v, auto simple_tag) {
+        constexpr bool SIMPLE = decltype(simple_tag)::value;
+        if (SIMPLE && u >= HALO) put(gi, u, v);
+        else if ((outm >> u) & 1u) put(gi, u, v);
+      };
+      float ss[16];
+      // One group's columns.  Rows in descending order, so each x is
+      // overwritten only after the three rows after it have read it; one row
+      // per scheduling group (the scheduler would otherwise hoist every row's
+      // exp and keep all conv results live at once).  NORM keeps y in place
+      // of x and sums its squares; else y leaves at once.
+      auto conv_rows = [&](auto gi_c, auto norm_tag) {
+        constexpr bool NORM = decltype(norm_tag)::value;
+        constexpr int gi = decltype(gi_c)::value, q = hd * GH + gi, j0 = q * JG;
+        // conv taps (row t - d) with the fp8 column scale and -log2(e) folded
+        // in: the conv yields z = -log2(e) c, so e^-c = 2^z and
+        // SiLU(c) = z / (-log2(e) (1 + 2^z)).  Loaded per group: all of them
+        // up front would spill.
+        float tp[JG][4];
+        const bool pad = pad_lane(q);
+        {
+          // first channel of the lane's JG (a pad lane: the head's last JG)
+          const int ch0 = pad ? real_col<RECT, D>(a, nb) + a.k_real - JG : real_col<RECT, D>(a, nb + GW * gi + JG * lc);
+          if (tap_mode == 1) {
+            const uint4* p = reinterpret_cast<const uint4*>(static_cast<const uint16_t*>(a.conv_w) + (int64_t)ch0 * 4);
 #pragma unroll
-                for (int jj = 0; jj < JB; ++jj)
-                  v[jj] = tile_take(acc[u >> 2][j0 + jj])[u & 3] * bf16_bits_to_f32(sc_raw[j0 + jj]);
-                if (tail_bf16) {
+            for (int jj = 0; jj < JG; jj += 2) {
+              const uint4 v = p[jj / 2];
+              const uint32_t t[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                  for (int jj = 0; jj < JB; ++jj) static_cast<uint16_t*>(a.tail)[at + jj * w1] = f32_to_bf16_bits(v[jj]);
-                } else {
+              for (int d = 0; d < 4; ++d)
 #pragma unroll
-                  for (int jj = 0; jj < JB; ++jj) static_cast<float*>(a.tail)[at + jj * w1] = v[jj];
+                for (int e = 0; e < 2; ++e) {
+                  const uint32_t pair = t[2 * e + ((3 - d) >> 1)];
+                  tp[jj + e][d] = __uint_as_float((d & 1) ? pair << 16 : pair & 0xffff0000u);
+                }
+            }
+          } else if (tap_mode == 2) {
+            const float4* p = reinterpret_cast<const float4*>(static_cast<const float*>(a.conv_w) + (int64_t)ch0 * 4);
+#pragma unroll
+            for (int jj = 0; jj < JG; ++jj) {
+              const float4 v = p[jj];
+              tp[jj][3] = v.x;
+              tp[jj][2] = v.y;
+              tp[jj][1] = v.z;
+              tp[jj][0] = v.w;
+            }
+          } else {
+#pragma unroll
+            for (int jj = 0; jj < JG; ++jj)
+#pragma unroll
+              for (int d = 0; d < 4; ++d) {
+                tp[jj][d] = 0.f;
+                if (d < a.w) {
+                  const int64_t i = (int64_t)(ch0 + jj) * a.w + a.w - 1 - d;   // tap of row t - d
+                  tp[jj][d] = a.conv_bf16 ? bf16_bits_to_f32(static_cast<const uint16_t*>(a.conv_w)[i])
+                                          : static_cast<const float*>(a.conv_w)[i];
                 }
               }
+          }
+#pragma unroll
+          for (int jj = 0; jj < JG; ++jj) {
+            const float sc = scale(j0 + jj) * -kLog2e;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) tp[jj][d] *= sc;
+          }
+        }
+        f32x4 x[JG], up[JG];       // rows 4 i .. 4 i + 3, and the four above them
+#pragma unroll
+        for (int jj = 0; jj < JG; ++jj) up[jj] = tile_take(acc[3][j0 + jj]);
+#pragma unroll
+        for (int i = 3; i >= 0; --i) {
+#pragma unroll
+          for (int jj = 0; jj < JG; ++jj) {
+            x[jj] = up[jj];
+            if (i > 0) {
+              up[jj] = tile_take(acc[i > 0 ? i - 1 : 0][j0 + jj]);
+            } else {
+#pragma unroll
+              for (int k = 0; k < 3; ++k) up[jj][1 + k] = rbase == 0 ? 0.f : above[8 * k + j0 + jj];
             }
           }
-        }
-      }
-      // destination of the lane's JB columns, row rbase
-      const int hh = is_q ? nb / D : (is_k ? (nb - a.C_q) / D : (nb - a.C_k) / D);
-      uint16_t* dst = static_cast<uint16_t*>(is_q ? a.Qbuf : (is_k ? a.Kbuf : a.Vbuf)) + ((int64_t)hh * T + t0) * D + JB * lc;
-      // RECT values: value head h (v_head = 2 k_real columns) is stored as
-      // two halves 2 h + e of k_real columns, each padded to D like a key head
-      // ([2 H_v][T][D]); the lanes of a half's last D - k_real columns also
-      // write its pad columns (zeros).
-      bool vpad = false;
-      if constexpr (RECT) {
-        if (!is_k) {
-          const int c = nb - a.C_k + JB * lc, h = c / a.v_head, c0 = c - h * a.v_head;
-          const int e = c0 / a.k_real, col = c0 - e * a.k_real;
-          dst = static_cast<uint16_t*>(a.Vbuf) + ((int64_t)(2 * h + e) * T + t0) * D + col;
-          vpad = col + (D - a.k_real) >= a.k_real;
-        }
-      }
-      auto put = [&](int u, const uint32_t* v) {
-        store_bf16<JB>(dst + (int64_t)u * D, v);
-        if (RECT && vpad) {
-          const uint32_t z[4] = {0u, 0u, 0u, 0u};
-          store_bf16<JB>(dst + (int64_t)u * D + (D - a.k_real), z);
-        }
-      };
-      // store of row u.  SIMPLE: only the tile's first rows may not be output
-      auto row_out = [&](int u, const uint32_t* v, auto simple_tag) {
-        constexpr bool SIMPLE = decltype(simple_tag)::value;
-        if (SIMPLE && u >= HALO) put(u, v);
-        else if ((outm >> u) & 1u) put(u, v);
-      };
-      // Rows in descending order, so each x is overwritten only after the
-      // three rows after it have read it; one row of the head's blocks per
-      // group (the scheduler would otherwise hoist every row's exp and keep
-      // all conv results live at once).  NORM keeps y in place of x and sums
-      // its squares; else y leaves at once.
-      float ss[32];
-      auto conv_rows = [&](auto norm_tag) {
-        constexpr bool NORM = decltype(norm_tag)::value;
-        f32x4 x[JB], up[JB];       // rows 4 i .. 4 i + 3, and the four above them
-#pragma unroll
-        for (int jj = 0; jj < JB; ++jj) up[jj] = tile_take(acc[7][j0 + jj]);
-#pragma unroll
-        for (int i = 7; i >= 0; --i) {
-#pragma unroll
-          for (int jj = 0; jj < JB; ++jj) {
-            x[jj] = up[jj];
-            up[jj] = i ? tile_take(acc[i ? i - 1 : 0][j0 + jj]) : f32x4{0.f, xp[0][j0 + jj], xp[1][j0 + jj], xp[2][j0 + jj]};
-          }
-          f32x4 y[JB];
+          f32x4 y[JG];
           auto four_rows = [&](auto mask_tag) {
             constexpr bool MASK = decltype(mask_tag)::value;
 #pragma unroll
             for (int r = 3; r >= 0; --r) {
               const int u = 4 * i + r;
               float sq = 0.f;
-              static_for<JB>([&](auto jj_c) {
-                constexpr int jj = decltype(jj_c)::value, j = j0 + jj;
+              static_for<JG>([&](auto jj_c) {
+                constexpr int jj = decltype(jj_c)::value;
                 const float x1 = r >= 1 ? x[jj][(r + 3) & 3] : up[jj][3];
                 const float x2 = r >= 2 ? x[jj][(r + 2) & 3] : up[jj][(r + 2) & 3];
                 const float x3 = r >= 3 ? x[jj][0] : up[jj][(r + 1) & 3];
-                float z = tp[j][0] * x[jj][r];
-                z = fmaf(tp[j][1], MASK && !((m1 >> u) & 1u) ? 0.f : x1, z);
-                z = fmaf(tp[j][2], MASK && !((m2 >> u) & 1u) ? 0.f : x2, z);
-                z = fmaf(tp[j][3], MASK && !((m3 >> u) & 1u) ? 0.f : x3, z);
-                if (RECT && NORM) z = pad_lane ? 0.f : z;
+                float z = tp[jj][0] * x[jj][r];
+                z = fmaf(tp[jj][1], MASK && !((m1 >> u) & 1u) ? 0.f : x1, z);
+                z = fmaf(tp[jj][2], MASK && !((m2 >> u) & 1u) ? 0.f : x2, z);
+                z = fmaf(tp[jj][3], MASK && !((m3 >> u) & 1u) ? 0.f : x3, z);
+                if (RECT && NORM) z = pad ? 0.f : z;
                 float v = z * __builtin_amdgcn_rcpf(fmaf(__builtin_amdgcn_exp2f(z), -kLog2e, -kLog2e));
                 if (NORM) asm volatile("" : "+v"(v));   // materialise y here, not at the stores
                 y[jj][r] = v;
                 sq = fmaf(v, v, sq);
               });
               if constexpr (NORM) {
-                ss[u] = sq;
+                ss[u] = gi ? ss[u] + sq : sq;
               } else {
-                uint32_t v[JB / 2];
-                static_for<JB / 2>([&](auto h_c) {
-                  constexpr int h = decltype(h_c)::value;
-                  v[h] = pack_bf16x2(y[2 * h][r], y[2 * h + 1][r]);
-                });
-                row_out(u, v, std::integral_constant<bool, !MASK>{});
+                uint32_t v[JG / 2];
+#pragma unroll
+                for (int h = 0; h < JG / 2; ++h) v[h] = pack_bf16x2(y[2 * h][r], y[2 * h + 1][r]);
+                row_out(gi, u, v, std::integral_constant<bool, !MASK>{});
               }
               __builtin_amdgcn_sched_barrier(0);
             }
           };
           if (wave_fast) four_rows(std::false_type{});
           else four_rows(std::true_type{});
-          if constexpr (NORM)
-            static_for<JB>([&](auto jj_c) {
-              constexpr int jj = decltype(jj_c)::value;
-              tile_put(acc[i][j0 + jj], y[jj]);
-            });
+          if constexpr (NORM) {
+#pragma unroll
+            for (int jj = 0; jj < JG; ++jj) tile_put(acc[i][j0 + jj], y[jj]);
+          }
         }
       };
+      if (tail_rows) {
+        // the raw projection of the segment's last w-1 rows is the conv state
+        static_for<GH>([&](auto gi_c) {
+          constexpr int gi = decltype(gi_c)::value, q = hd * GH + gi, j0 = q * JG;
+          const bool pad = pad_lane(q);
+          const int ch0 = pad ? 0 : real_col<RECT, D>(a, nb + GW * gi + JG * lc);
+          float sc[JG];
+#pragma unroll
+          for (int jj = 0; jj < JG; ++jj) sc[jj] = scale(j0 + jj);
+          static_for<16>([&](auto u_c) {
+            constexpr int u = decltype(u_c)::value;
+            if ((tail_rows >> u) & 1u) {
+              float v[JG];
+#pragma unroll
+              for (int jj = 0; jj < JG; ++jj) v[jj] = tile_take(acc[u >> 2][j0 + jj])[u & 3] * sc[jj];
+              if (((tailm >> u) & 1u) && !pad) {
+                const RowInfo ri = a.info[t0 + u];
+                if (ri.slot >= 0) {
+                  const int64_t at = ((int64_t)ri.slot * a.c_tail + a.tail_kv_off + ch0) * w1 + (w1 - ri.rem);
+                  if (tail_bf16) {
+#pragma unroll
+                    for (int jj = 0; jj < JG; ++jj) static_cast<uint16_t*>(a.tail)[at + jj * w1] = f32_to_bf16_bits(v[jj]);
+                  } else {
+#pragma unroll
+                    for (int jj = 0; jj < JG; ++jj) static_cast<float*>(a.tail)[at + jj * w1] = v[jj];
+                  }
+                }
+              }
+            }
+          });
+        });
+      }
       if (!is_k) {
-        conv_rows(std::false_type{});
+        static_for<GH>([&](auto gi_c) { conv_rows(gi_c, std::false_type{}); });
+        if constexpr (RECT) {
+          const uint32_t z[2] = {0u, 0u};
+#pragma unroll
+          for (int gi = 0; gi < GH; ++gi)
+            if (vpad[gi]) {
+#pragma clang loop unroll(disable)
+              for (int u = 0; u < 16; ++u)
+                if ((outm >> u) & 1u) store_bf16<JG>(dst[gi] + u * D + (D - a.k_real), z);
+            }
+        }
       } else {
-        conv_rows(std::true_type{});
+        static_for<GH>([&](auto gi_c) { conv_rows(gi_c, std::true_type{}); });
         // sum of squares of each row over the head's D columns: over the
         // lane's columns above, then across the group's 16 lanes
-        // (reduce-scatter: lane lc ends with rows tau and tau + 1)
-        bfly_step<32, 0, 0xB1>(ss, lc);    // quad_perm 1,0,3,2: lane ^ 1
-        bfly_step<16, 1, 0x4E>(ss, lc);    // quad_perm 2,3,0,1: lane ^ 2
-        bfly_step<8, 2, 0x124>(ss, lc);    // row_ror 4: bit 2 flipped
-        bfly_step<4, 3, 0x128>(ss, lc);    // row_ror 8: lane ^ 8
-        const int tau = (int)(__builtin_bitreverse32((uint32_t)lc) >> 27);   // 2 bitrev4(lc)
-        lfloat* ivp = INV + ((wid * 4 + g) * NH + hd) * 32;
-        const float qs = is_q ? a.q_scale : 1.f;
-        ivp[tau] = qs * __builtin_amdgcn_rsqf(ss[0] + a.eps);
-        ivp[tau + 1] = qs * __builtin_amdgcn_rsqf(ss[1] + a.eps);
+        // (reduce-scatter: lane lc ends with row bitrev4(lc))
+        bfly_step<16, 0, 0xB1>(ss, lc);    // quad_perm 1,0,3,2: lane ^ 1
+        bfly_step<8, 1, 0x4E>(ss, lc);     // quad_perm 2,3,0,1: lane ^ 2
+        bfly_step<4, 2, 0x124>(ss, lc);    // row_ror 4: bit 2 flipped
+        bfly_step<2, 3, 0x128>(ss, lc);    // row_ror 8: lane ^ 8
+        lfloat* ivp = INV + ((wid * 4 + g) * NH + hd) * 16;
+        ivp[__builtin_bitreverse32((uint32_t)lc) >> 28] =
+            (is_q ? a.q_scale : 1.f) * __builtin_amdgcn_rsqf(ss[0] + a.eps);
         // LDS operations of one wave complete in order: the reads below see
         // every lane's writes
-        auto out_rows = [&](auto simple_tag) {
+        static_for<GH>([&](auto gi_c) {
+          constexpr int gi = decltype(gi_c)::value, j0 = (hd * GH + gi) * JG;
+          auto out_rows = [&](auto simple_tag) {
 #pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const nf32x4 iv = *reinterpret_cast<const __attribute__((address_space(3))) nf32x4*>(ivp + 4 * q);
-            f32x4 y[JB];
+            for (int i = 0; i < 4; ++i) {
+              const nf32x4 iv = *reinterpret_cast<const __attribute__((address_space(3))) nf32x4*>(ivp + 4 * i);
+              f32x4 y[JG];
 #pragma unroll
-            for (int jj = 0; jj < JB; ++jj) y[jj] = tile_take(acc[q][j0 + jj]);
+              for (int jj = 0; jj < JG; ++jj) y[jj] = tile_take(acc[i][j0 + jj]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              uint32_t v[JB / 2];
+              for (int e = 0; e < 4; ++e) {
+                uint32_t v[JG / 2];
 #pragma unroll
-              for (int h = 0; h < JB / 2; ++h) v[h] = pack_bf16x2(y[2 * h][e] * iv[e], y[2 * h + 1][e] * iv[e]);
-              row_out(4 * q + e, v, simple_tag);
+                for (int h = 0; h < JG / 2; ++h) v[h] = pack_bf16x2(y[2 * h][e] * iv[e], y[2 * h + 1][e] * iv[e]);
+                row_out(gi, 4 * i + e, v, simple_tag);
+              }
             }
-          }
-        };
-        if (wave_fast) out_rows(std::true_type{});
-        else out_rows(std::false_type{});
+          };
+          if (wave_fast) out_rows(std::true_type{});
+          else out_rows(std::false_type{});
+        });
       }
     } else if (nb < a.C_z) {
       // ---- z head (output gate): the raw projection, bf16, head-major
-      uint16_t* dst = static_cast<uint16_t*>(a.Zbuf) + ((int64_t)((nb - a.C_kv) / D) * T + t0) * D + JB * lc;
+      static_for<GH>([&](auto gi_c) {
+        constexpr int gi = decltype(gi_c)::value, j0 = (hd * GH + gi) * JG;
+        uint16_t* dst = static_cast<uint16_t*>(a.Zbuf) + ((int64_t)((nb - a.C_kv) / D) * T + t0) * D + GW * gi + JG * lc;
+        float sc[JG];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        f32x4 x[JB];
+        for (int jj = 0; jj < JG; ++jj) sc[jj] = scale(j0 + jj);
 #pragma unroll
-        for (int jj = 0; jj < JB; ++jj) x[jj] = tile_take(acc[q][j0 + jj]) * bf16_bits_to_f32(sc_raw[j0 + jj]);
+        for (int i = 0; i < 4; ++i) {
+          f32x4 x[JG];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          uint32_t v[JB / 2];
+          for (int jj = 0; jj < JG; ++jj) x[jj] = tile_take(acc[i][j0 + jj]) * sc[jj];
 #pragma unroll
-          for (int h = 0; h < JB / 2; ++h) v[h] = pack_bf16x2(x[2 * h][e], x[2 * h + 1][e]);
-          if ((outm >> (4 * q + e)) & 1u) store_bf16<JB>(dst + (int64_t)(4 * q + e) * D, v);
+          for (int e = 0; e < 4; ++e) {
+            uint32_t v[JG / 2];
+#pragma unroll
+            for (int h = 0; h < JG / 2; ++h) v[h] = pack_bf16x2(x[2 * h][e], x[2 * h + 1][e]);
+            if ((outm >> (4 * i + e)) & 1u) store_bf16<JG>(dst + (4 * i + e) * D, v);
+          }
         }
-      }
+      });
     } else {
       // ---- gate columns: G = log2 alpha from a, beta from b (no conv).  G
       // and beta are head-major ([H_v][T]): each 16-column block of raw
       // projections is transposed through the wave's LDS area (column pitch
-      // 128 rows, 16-byte chunks XOR-swizzled by the column: writes of 16
+      // 64 rows, 16-byte chunks XOR-swizzled by the column: writes of 16
       // columns and reads of one fall on distinct banks), then one column at
       // a time -- its gate wave-uniform -- is finished and stored, 64 rows of
       // one head per store.  Every row of the tile from hal on that lies
       // before T is an output (gates do not depend on the segments).
       lfloat* tw = (lfloat*)(smem_raw + GATE_OFF + wid * GATE_WAVE);
-      static_for<JB>([&](auto jj_c) {
-        constexpr int jj = decltype(jj_c)::value, j = j0 + jj;
+      const int r = wm * 64 + lane;                // the tile row this lane stores
+      const bool st_ok = r >= hal && row0 + r < T;
+      static_for<D / 16>([&](auto jj_c) {
+        constexpr int jj = decltype(jj_c)::value, j = hd * (D / 16) + jj;
         const int nb_j = nb + 16 * jj;             // first column of the block (wave-uniform)
         if (nb_j < a.N) {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) {
+          for (int i = 0; i < 4; ++i) {
             const f32x4 v = tile_take(acc[i][j]);
-            st_f4(tw + lc * 128 + (((8 * g + i) ^ lc) << 2), v[0], v[1], v[2], v[3]);
+            st_f4(tw + lc * 64 + (((4 * g + i) ^ lc) << 2), v[0], v[1], v[2], v[3]);
           }
           // LDS operations of one wave complete in order: the reads below
           // see every lane's writes
@@ -625,15 +632,9 @@ __global__ __launch_bounds__(kTileThreads, 1) void proj_conv_kernel(ProjConvBatc
             const bool is_a = n < a.C_z + a.H_v;
             const int hv = is_a ? n - a.C_z : n - a.C_z - a.H_v;
             const float sc = col_scale<TB>(a, real_col<RECT, D>(a, n));
-            const float al = is_a ? -__expf(a.a_log[hv]) * kLog2e : 0.f, db = is_a ? a.dt_bias[hv] : 0.f;
-            float* dst = (is_a ? a.Gbuf : a.Bbuf) + (int64_t)hv * T;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const int r = 64 * h + lane;         // the row this lane stores
-              const float x = tw[c * 128 + (((r >> 2) ^ c) << 2) + (r & 3)] * sc;
-              const float v = is_a ? al * softplus(x + db) : fast_sigmoid(x);
-              if (wm * 128 + r >= hal && row0 + wm * 128 + r < T) dst[row0 + wm * 128 + r] = v;
-            }
+            const float x = tw[c * 64 + (((lane >> 2) ^ c) << 2) + (lane & 3)] * sc;
+            const float v = is_a ? -__expf(a.a_log[hv]) * kLog2e * softplus(x + a.dt_bias[hv]) : fast_sigmoid(x);
+            if (st_ok) ((is_a ? a.Gbuf : a.Bbuf) + (int64_t)hv * T)[row0 + r] = v;
           }
         }
       });

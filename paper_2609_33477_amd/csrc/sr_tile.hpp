@@ -6,14 +6,18 @@
 //  - v_mfma_f32_16x16x32_bf16: it reads and writes half the accumulator bits
 //    per multiply-add of the 32x32x16 form, which at the same issue rate
 //    settled at a lower clock.
-//  - 4 waves of 128 x 128, one per SIMD, the 256 accumulators in AGPRs: 64 KB
-//    of fragment reads per 32 of K instead of the 96 KB of 8 waves of 64 x 128.
 //  - K-steps of 64: every row a DMA fetches is a whole 128-byte line (bf16),
 //    half the L2 requests of 64-byte rows.
+//  - 8 waves of 64 x 128 (two per SIMD), accumulators in AGPRs.  4 waves of
+//    128 x 128 read a third fewer fragments and run the plain loop 0 to 2%
+//    faster, but leave one wave per SIMD for everything around it, and one
+//    wave issues a VALU instruction every ~5 cycles: the projection's
+//    epilogue took 25K cycles a tile that way, a fifth of its time.
 // Plain GEMM of the varlen projection's shape (36864 x 6144 x 2560, normal
-// inputs, one card): 8 waves on 32x32x16 with K-steps of 32 1029 us; 4 waves,
-// K-steps of 64 965 us; the same on 16x16x32 868 us; the hand-over moved into
-// the first half step and the DMAs spread over the step 817 us (1.42 PFLOP/s).
+// inputs, one card): 32x32x16 with K-steps of 32 1029 us, with K-steps of 64
+// (4 waves) 965 us, the same on 16x16x32 868 us; the hand-over moved into the
+// first half step and the DMAs spread over the step 808 us (1.44 PFLOP/s; 4
+// waves 807 us).
 //
 // LDS (160 KB).  bf16 B: a ring of five 32 KB half stages (A or B of one
 // K-step), A(k) in slot 2k mod 5, B(k) in 2k + 1 mod 5.  fp8 B: three 32 KB A
@@ -23,14 +27,14 @@
 // One hand-over (wait + barrier) per K-step, after MFMA kBarrierAt of the
 // first half step: by then every wave has read its second-half fragments, so
 // the step's slots are free, and the next step's rows have landed.  The
-// refills follow it, one DMA per few MFMAs (issued back to back they cost
-// 6%), until the step's end.
+// refills follow it, one DMA per few MFMAs (issued closer together they cost
+// up to 6%), until the step's end.
 //
 // The MFMAs are inline asm with AGPR accumulators: left to itself the
 // compiler put part of the accumulators in VGPRs and copied them around the
 // loop (180 to 500 moves per K-step, half the speed).  The asm hides them
 // from its hazard bookkeeping, so the code keeps the distances itself: the
-// fp8 conversions feeding an MFMA are issued at least three MFMAs before it,
+// fp8 conversions feeding an MFMA are issued at least four instructions before it,
 // and the loop ends by letting the last products land before anyone reads them.
 #pragma once
 
@@ -41,10 +45,10 @@
 namespace sr {
 
 constexpr int kTileM = 256, kTileN = 256, kTileK = 64;
-constexpr int kTileThreads = 256, kTileWaves = 4;
+constexpr int kTileThreads = 512, kTileWaves = 8;
 constexpr int kTileLds = 160 * 1024;
 constexpr int kTileHalf = 256 * 128;    // bytes of one K-step of A (and of bf16 B)
-constexpr int kBarrierAt = 48;
+constexpr int kBarrierAt = 28;
 
 typedef __attribute__((address_space(3))) char tile_lds;
 typedef unsigned int tile_u32x4 __attribute__((ext_vector_type(4)));
@@ -58,29 +62,29 @@ __device__ __forceinline__ uint4 tile_ld16(const tile_lds* p) {
 // once the next step has landed, and before the first step
 template <typename TB> struct TileB;
 template <> struct TileB<bf16_t> {
-  static constexpr int ROW = 128, DMAS = 8, AHEAD = 2, SPACING = 5, PENDING = 8, PENDING0 = 24;
+  static constexpr int ROW = 128, DMAS = 4, AHEAD = 2, SPACING = 4, PENDING = 4, PENDING0 = 12;
 };
 template <> struct TileB<fp8_t> {
-  static constexpr int ROW = 64, DMAS = 4, AHEAD = 4, SPACING = 6, PENDING = 12, PENDING0 = 28;
+  static constexpr int ROW = 64, DMAS = 2, AHEAD = 4, SPACING = 5, PENDING = 6, PENDING0 = 14;
 };
 constexpr int kTileAheadA = 3;          // K-steps ahead of A
 
 // Chunk swizzles: LDS row r keeps 16-byte chunk c of its K-step at c ^ swz(r).
-// A fragment reads rows 32 (m / 4) + 4 i + m % 4 (m = lane % 16), a B one 16
+// An A fragment reads rows 16 (m / 4) + 4 i + m % 4 (m = lane % 16), a B one 16
 // consecutive rows.
-__device__ __forceinline__ int tile_swz_a(int r) { return ((r >> 1) & 1) | ((r >> 4) & 6); }
+__device__ __forceinline__ int tile_swz_a(int r) { return ((r >> 1) & 1) | ((r >> 3) & 6); }
 template <typename TB>
 __device__ __forceinline__ int tile_swz_b(int r) {
   return std::is_same<TB, bf16_t>::value ? (r >> 1) & 7 : (r >> 2) & 3;
 }
 
 // Tile row / chunk that lane `lane` of wave `wid` fetches with its DMA i (the
-// LDS side is linear: block wid * 8 + i, 16 bytes per lane)
-__device__ __forceinline__ int tile_a_row(int wid, int i, int lane) { return (wid * 8 + i) * 8 + (lane >> 3); }
+// LDS side is linear: A block wid * 4 + i, 16 bytes per lane)
+__device__ __forceinline__ int tile_a_row(int wid, int i, int lane) { return (wid * 4 + i) * 8 + (lane >> 3); }
 __device__ __forceinline__ int tile_a_chunk(int row, int lane) { return (lane & 7) ^ tile_swz_a(row); }
 template <typename TB>
 __device__ __forceinline__ int tile_b_row(int wid, int i, int lane) {
-  return std::is_same<TB, bf16_t>::value ? (wid * 8 + i) * 8 + (lane >> 3) : (wid * 4 + i) * 16 + (lane >> 2);
+  return std::is_same<TB, bf16_t>::value ? (wid * 4 + i) * 8 + (lane >> 3) : (wid * 2 + i) * 16 + (lane >> 2);
 }
 template <typename TB>
 __device__ __forceinline__ int tile_b_chunk(int row, int lane) {
@@ -88,7 +92,7 @@ __device__ __forceinline__ int tile_b_chunk(int row, int lane) {
 }
 
 // Accumulators of wave (wm, wn) = (wid / 2, wid % 2): acc[i][j][r] of lane l
-// is tile row 128 wm + 32 (l / 16) + 4 i + r -- 32 consecutive rows per lane
+// is tile row 64 wm + 16 (l / 16) + 4 i + r -- 16 consecutive rows per lane
 // over i and r -- and LDS row 128 wn + 16 j + l % 16 of B.
 //
 // hardware block id -> (m tile, n tile): contiguous runs per XCD (blocks are
@@ -112,9 +116,9 @@ __device__ __forceinline__ void tile_of(int b, int tm, int tn, int& mt, int& nt)
 // Accumulators stay in AGPRs across the epilogue too (moved to VGPRs as a
 // whole they spill): tile_pin() ties them there, then four rows of a column
 // block at a time are copied out by tile_take() and back by tile_put().
-__device__ __forceinline__ void tile_pin(f32x4 (&acc)[8][8]) {
+__device__ __forceinline__ void tile_pin(f32x4 (&acc)[4][8]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j) asm volatile("" : "+a"(acc[i][j]));
 }
@@ -133,7 +137,7 @@ __device__ __forceinline__ void tile_put(f32x4& a, f32x4 v) {
 // blocks of B this wave multiplies (8, or fewer where the rest lies past N: it
 // keeps its DMA share and every barrier).  KT = K / 64 >= 1.
 template <typename TB, int NJ>
-__device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a_base, const uint32_t (&a_off)[8],
+__device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[4][8], const char* a_base, const uint32_t (&a_off)[4],
                                                const char* (&b_ptr)[TileB<TB>::DMAS], int KT, char* smem_raw, int wid,
                                                int lane) {
   using B = TileB<TB>;
@@ -144,7 +148,7 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
   const int wm = wid >> 1, wn = wid & 1, lc = lane & 15, g = lane >> 4;
 
-  const int arow = wm * 128 + 32 * (lc >> 2) + (lc & 3), brow = wn * 128 + lc;
+  const int arow = wm * 64 + 16 * (lc >> 2) + (lc & 3), brow = wn * 128 + lc;
   // A chunk of half step s: 4 s + g; fp8: 2 g + s, so that one 16-byte read of
   // B holds the lane's bytes of both half steps
   int a_k[2], b_k[2];
@@ -154,9 +158,10 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
     b_k[s] = B0 + brow * B::ROW + ((FP8 ? g : 4 * s + g) ^ tile_swz_b<TB>(brow)) * 16;
   }
 
-  bf16x8 fa[2][8];
-  bf16x8 fb[2][FP8 ? 1 : 8];     // bf16 B fragments by half step; fp8: [j % 2] converted
-  uint4 raw[FP8 ? 8 : 1];        // fp8 fragments of the K-step
+  bf16x8 fa[2][4];
+  bf16x8 fb[2][8];               // B fragments by half step (bf16)
+  uint4 raw[8];                  // fp8 fragments of the K-step
+  uint32_t conv[4][4];           // fp8 fragments converted, [j % 4]
   auto read_a = [&](int slot, int s, int i) { fa[s][i] = as_bf16x8(tile_ld16(smem + slot + a_k[s] + i * 4 * 128)); };
   auto read_b = [&](int slot, int s, int j) {
     if (j >= NJ) return;
@@ -169,25 +174,21 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
     if constexpr (FP8) {
       if (j >= NJ) return;
       const uint32_t w = s ? (c < 2 ? raw[j].z : raw[j].w) : (c < 2 ? raw[j].x : raw[j].y);
-      uint4 o = __builtin_bit_cast(uint4, fb[j & 1][0]);
-      const uint32_t v = (c & 1) ? __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true))
-                                 : __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false));
-      if (c == 0) o.x = v;
-      else if (c == 1) o.y = v;
-      else if (c == 2) o.z = v;
-      else o.w = v;
-      fb[j & 1][0] = as_bf16x8(o);
+      if (c & 1) conv[j & 3][c] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, true));
+      else conv[j & 3][c] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, false));
     }
   };
-  // MFMA q of a half step: fragment j = q / 8 of B against all of A
+  // MFMA q of a half step: fragment j = q / 4 of B against all of A
   auto mma = [&](int s, int q) {
-    const int j = q >> 3, i = q & 7;
-    if (j < NJ)
-      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
-                   : "+a"(acc[i][j])
-                   : "v"(fa[s][i]), "v"(FP8 ? fb[j & 1][0] : fb[s][FP8 ? 0 : j]));
+    const int j = q >> 2, i = q & 3;
+    if (j < NJ) {
+      bf16x8 b;
+      if constexpr (FP8) b = as_bf16x8(make_uint4(conv[j & 3][0], conv[j & 3][1], conv[j & 3][2], conv[j & 3][3]));
+      else b = fb[s][j];
+      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[i][j]) : "v"(fa[s][i]), "v"(b));
+    }
   };
-  auto dma_a = [&](int slot, int i) { dma16_s(a_base, a_off[i], lds0 + slot + (wid * 8 + i) * 1024); };
+  auto dma_a = [&](int slot, int i) { dma16_s(a_base, a_off[i], lds0 + slot + (wid * 4 + i) * 1024); };
   auto dma_b = [&](int slot, int i) { dma16(b_ptr[i], lds0 + B0 + slot + (wid * NB + i) * 1024); };
   // sources advance one K-step after their last DMA of a step; not past the
   // last K-step (the prologue of a short K refetches it)
@@ -202,7 +203,7 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
   for (int k = 0; k < 4; ++k) {
     if (k < kTileAheadA) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) dma_a(FP8 ? k * kTileHalf : (2 * k % 5) * kTileHalf, i);
+      for (int i = 0; i < 4; ++i) dma_a(FP8 ? k * kTileHalf : (2 * k % 5) * kTileHalf, i);
       next_a(k + 1 < KT);
     }
     if (k < B::AHEAD) {
@@ -218,9 +219,9 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
 #pragma unroll
   for (int q = 0; q < 8; ++q) read_b(sb, 0, q);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) read_a(sa, 0, q);
+  for (int q = 0; q < 4; ++q) read_a(sa, 0, q);
 #pragma unroll
-  for (int c = 0; c < 4; ++c) cvt(0, 0, c);
+  for (int c = 0; c < 8; ++c) cvt(0, c >> 2, c & 3);
   __builtin_amdgcn_sched_barrier(0);
 
   // One K-step.  DB / DA: refill B (AHEAD steps on) and A; W: DMAs of this
@@ -245,29 +246,29 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
         dma_b(FP8 ? sb : sa, d);
         if (d == NB - 1) next_b(true);
       }
-      if (DA && d >= NB && d < NB + 8) {
+      if (DA && d >= NB && d < NB + 4) {
         dma_a(FP8 ? sa : sb, d - NB);
-        if (d == NB + 7) next_a(true);
+        if (d == NB + 3) next_a(true);
       }
     };
-    static_assert((NB + 8) * B::SPACING <= 128 - kBarrierAt, "the refills fit behind the hand-over");
+    static_assert((NB + 4) * B::SPACING <= 64 - kBarrierAt, "the refills fit behind the hand-over");
+    // read r of a half step's fragments, in the order the MFMAs need them: B 0,
+    // A 0..3, B 1..7 (fp8 B is read once a step, below)
+    auto read_half = [&](int ra, int rb, int s, int r) {
+      if (FP8) {
+        if (r < 4) read_a(ra, s, r);
+      } else if (r < 12) {
+        if (r == 0) read_b(rb, s, 0);
+        else if (r <= 4) read_a(ra, s, r - 1);
+        else read_b(rb, s, r - 4);
+      }
+    };
 #pragma unroll
-    for (int q = 0; q < 64; ++q) {
+    for (int q = 0; q < 32; ++q) {
       mma(0, q);
-      if (q % 2 == 0) {                                 // second-half fragments of this step
-        const int r = q / 2;
-        if (FP8) {
-          if (r < 8) read_a(sa, 1, r);
-        } else if (r < 16) {
-          if (r == 0) read_b(sb, 1, 0);
-          else if (r <= 8) read_a(sa, 1, r - 1);
-          else read_b(sb, 1, r - 8);
-        }
-      }
-      if ((q & 7) >= 1 && (q & 7) <= 4) {               // the next fragment's conversion
-        if (q < 56) cvt(0, (q >> 3) + 1, (q & 7) - 1);
-        else cvt(1, 0, (q & 7) - 1);
-      }
+      if (q % 2 == 0) read_half(sa, sb, 1, q / 2);      // second-half fragments of this step
+      if (q < 24) cvt(0, (q >> 2) + 2, q & 3);          // two fragments ahead
+      else cvt(1, (q >> 2) - 6, q & 3);
       __builtin_amdgcn_sched_barrier(0);
       if (q == kBarrierAt - 1 && !LAST) {
         // this wave's reads of the step's slots are complete and its DMAs of
@@ -283,24 +284,15 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
       }
     }
 #pragma unroll
-    for (int q = 0; q < 64; ++q) {
+    for (int q = 0; q < 32; ++q) {
       mma(1, q);
       if (!LAST) {                                      // first-half fragments of the next step
-        if constexpr (FP8) {
-          if (q % 2 == 0 && q < 16) read_a(na, 0, q / 2);
-          if ((q & 7) == 0) read_b(nb, 0, q >> 3);      // raw[j] was converted for the last time in group j - 1
-        } else if (q % 2 == 0 && q < 32) {
-          const int r = q / 2;
-          if (r == 0) read_b(nb, 0, 0);
-          else if (r <= 8) read_a(na, 0, r - 1);
-          else read_b(nb, 0, r - 8);
-        }
+        if (q % 2 == 0) read_half(na, nb, 0, q / 2);
+        if (FP8 && q % 4 == 0) read_b(nb, 0, q >> 2);   // raw[j] was converted for the last time in group j - 2
       }
-      if ((q & 7) >= 1 && (q & 7) <= 4) {
-        if (q < 56) cvt(1, (q >> 3) + 1, (q & 7) - 1);
-        else if (!LAST) cvt(0, 0, (q & 7) - 1);
-      }
-      refill(q + 64 - kBarrierAt);
+      if (q < 24) cvt(1, (q >> 2) + 2, q & 3);
+      else if (!LAST) cvt(0, (q >> 2) - 6, q & 3);
+      refill(q + 32 - kBarrierAt);
       __builtin_amdgcn_sched_barrier(0);
     }
     sa = na;
@@ -311,10 +303,10 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[8][8], const char* a
   constexpr int TAIL = FP8 ? 4 : 3;      // last steps, whose refills would lie past K
   for (int kt = 0; kt < KT - TAIL; ++kt) step(T{}, T{}, std::integral_constant<int, B::PENDING>{}, F{});
   if constexpr (FP8) {
-    if (KT >= 4) step(F{}, T{}, std::integral_constant<int, 12>{}, F{});   // A(KT - 1)
-    if (KT >= 3) step(F{}, F{}, std::integral_constant<int, 8>{}, F{});
+    if (KT >= 4) step(F{}, T{}, std::integral_constant<int, 6>{}, F{});   // A(KT - 1)
+    if (KT >= 3) step(F{}, F{}, std::integral_constant<int, 4>{}, F{});
   } else {
-    if (KT >= 3) step(T{}, F{}, std::integral_constant<int, 8>{}, F{});    // B(KT - 1)
+    if (KT >= 3) step(T{}, F{}, std::integral_constant<int, 4>{}, F{});    // B(KT - 1)
   }
   if (KT >= 2) step(F{}, F{}, std::integral_constant<int, 0>{}, F{});
   step(F{}, F{}, std::integral_constant<int, 0>{}, T{});
@@ -336,9 +328,9 @@ __device__ __forceinline__ void tile_drain() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-__device__ __forceinline__ void tile_zero(f32x4 (&acc)[8][8]) {
+__device__ __forceinline__ void tile_zero(f32x4 (&acc)[4][8]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 }

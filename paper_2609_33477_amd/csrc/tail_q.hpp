@@ -6,7 +6,7 @@
 // tiles: they are dispatched into its last, partial round (or onto CUs its
 // tiles leave idle), so the tail costs no launch of its own.
 //
-// Block (4 waves): 32 tail rows x 32 q channels, on v_mfma_f32_32x32x16_bf16.
+// Block (8 waves): 32 tail rows x 32 q channels, on v_mfma_f32_32x32x16_bf16.
 // Anchor rows and W_q rows go global -> LDS by DMA in contiguous 1 KB runs
 // per row (a whole row of the 512-column stage per instruction), two stages
 // in flight, 16-byte chunks XOR-swizzled by (row & 15) so the fragment reads
@@ -26,7 +26,7 @@
 
 namespace sr {
 
-constexpr int kTqWaves = 4;
+constexpr int kTqWaves = 8;
 constexpr int kTqChunk = 512;                  // d_model columns per stage
 constexpr int kTqHalf = 32 * 1024;             // 32 rows x 1 KB
 constexpr int kTqStage = 2 * kTqHalf;          // anchor rows | weight rows
@@ -91,9 +91,8 @@ __device__ __forceinline__ void tail_q_block(const TailArgs& a, int bx, int by, 
     return;
   }
   constexpr int EB = sizeof(TW);            // weight bytes per element
-  constexpr int RPW = 32 / kTqWaves;        // rows each wave stages
-  constexpr int WDMA = RPW * EB / 2;        // weight DMAs per wave per stage: one row each (bf16), two rows (fp8)
-  constexpr int DPW = RPW + WDMA;           // DMAs per wave per stage
+  constexpr int WDMA = 2 * EB;              // weight DMAs per wave per stage: 4 (bf16, one row each), 2 (fp8, two rows)
+  constexpr int DPW = 4 + WDMA;             // DMAs per wave per stage
   const int c0 = bx * 32;
   const int D = a.D;
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
@@ -107,8 +106,8 @@ __device__ __forceinline__ void tail_q_block(const TailArgs& a, int bx, int by, 
     const int kc = min(kTqChunk, D - k0);
     const uint32_t st = lds0 + (ch & 1) * kTqStage;
 #pragma unroll
-    for (int j = 0; j < RPW; ++j) {
-      const int m = RPW * wid + j;
+    for (int j = 0; j < 4; ++j) {
+      const int m = 4 * wid + j;
       const int g = min(lane ^ tq_swz(m), kc / 8 - 1);
       dma16(xbase + (row_t[m] * D + k0) * 2 + g * 16, st + m * 1024);
     }
@@ -116,16 +115,16 @@ __device__ __forceinline__ void tail_q_block(const TailArgs& a, int bx, int by, 
     for (int j = 0; j < WDMA; ++j) {
       int m, p;
       if constexpr (EB == 2) {
-        m = RPW * wid + j;
+        m = 4 * wid + j;
         p = lane;
       } else {                                  // 512-byte fp8 rows: two per instruction
-        m = RPW * wid + 2 * j + (lane >> 5);
+        m = 4 * wid + 2 * j + (lane >> 5);
         p = lane & 31;
       }
       const int c = min(c0 + m, a.c_q - 1);
       const int g = min(p ^ tq_swz(m), kc * EB / 16 - 1);
       dma16(wbase + ((int64_t)c * D + k0) * EB + g * 16,
-            st + kTqHalf + (EB == 2 ? m * 1024 : (RPW * wid + 2 * j) * 512));
+            st + kTqHalf + (EB == 2 ? m * 1024 : (4 * wid + 2 * j) * 512));
     }
   };
   const int nch = (D + kTqChunk - 1) / kTqChunk;
