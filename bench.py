@@ -157,7 +157,7 @@ def algorithmic_work(wl, with_q=True):
 
 # sources each kernel is built from (the traffic record is void once they change)
 KERNEL_SOURCES = {
-    "proj_conv": ("proj_conv.hip", "tail_q.hpp", "sr_device.hpp", "sr_internal.hpp"),
+    "proj_conv": ("proj_conv.hip", "proj_conv_fp8.hip", "proj_conv_kernel.hpp", "sr_tile.hpp", "tail_q.hpp", "sr_device.hpp", "sr_internal.hpp"),
     "gdn_scan": ("gdn_scan_bf16.hip", "sr_device.hpp", "sr_internal.hpp"),
     "proj_gemm": ("proj_gemm.hip", "sr_device.hpp", "sr_internal.hpp"),
     "decay_state": ("decay_state.hip", "sr_device.hpp", "sr_internal.hpp"),

@@ -376,11 +376,12 @@ hipError_t tail_by_input(int ad, int wd, const TailArgs& a, hipStream_t s) {
 
 // The q-tail blocks of tail_q.hpp in a grid of their own (bf16 anchors on a
 // path without the fused projection)
+constexpr int kTqThreads = 512;
 template <typename TW>
-__global__ __launch_bounds__(64 * kTqWaves) void tail_q_kernel(TailArgs a) {
+__global__ __launch_bounds__(kTqThreads) void tail_q_kernel(TailArgs a) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
-  __shared__ __attribute__((aligned(1024))) char smem[kTqLds];
-  tail_q_block<TW>(a, blockIdx.x, blockIdx.y, smem);
+  __shared__ __attribute__((aligned(1024))) char smem[TqStage<512>::LDS];
+  tail_q_block<TW, kTqThreads / 64, TqStage<512>::LDS>(a, blockIdx.x, blockIdx.y, smem);
 }
 
 }  // namespace
@@ -402,8 +403,8 @@ hipError_t launch_tail(int anchor_dtype, int weight_dtype, int tail_dtype, const
   if (anchor_dtype == SR_BF16) {
     if (a.n_seg == 0 || a.w < 2 || a.c_tail == 0) return hipSuccess;
     const dim3 grid(tail_q_grid_x(a), tail_q_grid_y(a));
-    if (weight_dtype == SR_BF16) hipLaunchKernelGGL((tail_q_kernel<bf16_t>), grid, dim3(64 * kTqWaves), 0, s, a);
-    else if (weight_dtype == SR_FP8_E4M3) hipLaunchKernelGGL((tail_q_kernel<fp8_t>), grid, dim3(64 * kTqWaves), 0, s, a);
+    if (weight_dtype == SR_BF16) hipLaunchKernelGGL((tail_q_kernel<bf16_t>), grid, dim3(kTqThreads), 0, s, a);
+    else if (weight_dtype == SR_FP8_E4M3) hipLaunchKernelGGL((tail_q_kernel<fp8_t>), grid, dim3(kTqThreads), 0, s, a);
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }

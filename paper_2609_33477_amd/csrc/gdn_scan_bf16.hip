@@ -858,24 +858,11 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
   }
 }
 
-// Compute units of the current device (one workgroup fits per CU).
-int device_cus() {
-  static int cache[64];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cache[dev] == 0) {
-    int n = 0;
-    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cache[dev] = n;
-  }
-  return cache[dev];
-}
-
 template <int D, bool SPLIT = false>
 hipError_t run(const ScanArgs& a, hipStream_t s) {
   const int64_t units = (int64_t)a.n_seg * a.n_layers * a.H_v;
   if (units == 0) return hipSuccess;
-  // one workgroup per CU, each running its share of the units back to back
+  // one workgroup per CU (one fits), each running its share of the units back to back
   // (at most kScanUnits)
   int64_t grid = units < device_cus() ? units : device_cus();
   if (grid * kScanUnits < units) grid = (units + kScanUnits - 1) / kScanUnits;

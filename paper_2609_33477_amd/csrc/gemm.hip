@@ -25,33 +25,33 @@ namespace {
 __device__ __forceinline__ float silu(float x) { return x * __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
 
 template <int MODE>
-__global__ __launch_bounds__(kTileThreads, 1) void block_gemm_kernel(BlockGemmArgs a, int tiles_m, int tiles_n) {
+__global__ __launch_bounds__(kTileThreads<TileBig>, 1) void block_gemm_kernel(BlockGemmArgs a, int tiles_m, int tiles_n) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
-  __shared__ __attribute__((aligned(1024))) char smem[kTileLds];
+  __shared__ __attribute__((aligned(1024))) char smem[kTileLds<TileBig>];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wid >> 1, wn = wid & 1;
   const int lc = lane & 15, g = lane >> 4;
   int mt, nt;
   tile_of(blockIdx.x, tiles_m, tiles_n, mt, nt);
-  const int64_t row0 = (int64_t)mt * kTileM;
-  const int n0 = nt * kTileN;
+  const int64_t row0 = (int64_t)mt * TileBig::ROWS;
+  const int n0 = nt * TileBig::ROWS;
   const int K = a.K;
   const int64_t M = a.M;
 
   const char* a_base = static_cast<const char*>(a.A) + row0 * K * 2;
   uint32_t a_off[4];
-  const char* b_ptr[TileB<bf16_t>::DMAS];
+  const char* b_ptr[TileRing<TileBig, bf16_t>::DB];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     int row = tile_a_row(wid, i, lane);
-    const int chunk = tile_a_chunk(row, lane);
+    const int chunk = tile_a_chunk<TileBig>(row, lane);
     const int64_t last = M - 1 - row0;             // rows past M are never stored
     row = row < last ? row : (int)last;
     a_off[i] = (uint32_t)(row * (K * 2) + chunk * 16);
   }
 #pragma unroll
-  for (int i = 0; i < TileB<bf16_t>::DMAS; ++i) {
+  for (int i = 0; i < TileRing<TileBig, bf16_t>::DB; ++i) {
     const int row = tile_b_row<bf16_t>(wid, i, lane);
     const int h = row >> 7, j = (row >> 4) & 7, c = row & 15;   // column half, fragment block, lane
     const char* w;
@@ -67,7 +67,7 @@ __global__ __launch_bounds__(kTileThreads, 1) void block_gemm_kernel(BlockGemmAr
   }
   f32x4 acc[4][8];
   tile_zero(acc);
-  tile_main_loop<bf16_t, 8>(acc, a_base, a_off, b_ptr, K / kTileK, smem, wid, lane);
+  tile_main_loop<TileBig, bf16_t, 8>(acc, a_base, a_off, b_ptr, K / kTileK, smem, wid, lane);
 
   // ---- epilogue: acc[i][j][r] is tile row 64 wm + 16 g + 4 i + r of the
   // lane's block j
@@ -123,9 +123,9 @@ __global__ __launch_bounds__(kTileThreads, 1) void block_gemm_kernel(BlockGemmAr
 template <int MODE>
 hipError_t run_gemm(const BlockGemmArgs& a, hipStream_t s) {
   if (a.M == 0) return hipSuccess;
-  if (a.K < kTileK || a.K % kTileK || a.N % kTileN) return hipErrorInvalidValue;
-  const int tm = (int)((a.M + kTileM - 1) / kTileM), tn = a.N / kTileN;
-  hipLaunchKernelGGL((block_gemm_kernel<MODE>), dim3(tm * tn), dim3(kTileThreads), 0, s, a, tm, tn);
+  if (a.K < kTileK || a.K % kTileK || a.N % TileBig::ROWS) return hipErrorInvalidValue;
+  const int tm = (int)((a.M + TileBig::ROWS - 1) / TileBig::ROWS), tn = a.N / TileBig::ROWS;
+  hipLaunchKernelGGL((block_gemm_kernel<MODE>), dim3(tm * tn), dim3(kTileThreads<TileBig>), 0, s, a, tm, tn);
   return hipGetLastError();
 }
 

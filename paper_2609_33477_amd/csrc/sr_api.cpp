@@ -175,6 +175,18 @@ hipError_t sr::timed_launch(int kind, hipStream_t s, hipError_t (*launch)(void*)
   return timed(kind, s, [&] { return launch(ctx); });
 }
 
+int sr::device_cus() {
+  static int cache[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+  if (cache[dev] == 0) {
+    int n = 0;
+    if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+    cache[dev] = n;
+  }
+  return cache[dev];
+}
+
 hipError_t sr::note_error(int kind, hipError_t e) { return note(kind, e); }
 
 namespace {

@@ -116,6 +116,7 @@ struct ProjConvBatch {
 
 hipError_t launch_proj_conv(int weight_dtype, int d_head, const ProjConvBatch& b, hipStream_t s);
 hipError_t launch_proj_conv(int weight_dtype, int d_head, const ProjConvArgs& a, hipStream_t s);
+hipError_t launch_proj_conv_fp8(int d_head, const ProjConvBatch& b, hipStream_t s);   // by launch_proj_conv
 
 // --------------------------------------------------- conv, activations, gates
 struct ConvGateArgs {
@@ -151,6 +152,9 @@ hipError_t launch_conv_gate(int op_dtype, int conv_dtype, int tail_dtype, int d_
 // their own (the fused projection's grid carries them when it runs)
 hipError_t launch_tail(int anchor_dtype, int weight_dtype, int tail_dtype, const TailArgs& a,
                        hipStream_t s);
+
+// Compute units of the current device.
+int device_cus();
 
 // ------------------------------------------------------------ chunked scan
 constexpr int kScanMaxLayers = 32;
