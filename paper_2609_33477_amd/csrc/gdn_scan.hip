@@ -16,10 +16,16 @@
 // Only differences G_i - G_j <= 0 are exponentiated, so strong decay
 // underflows to zero instead of overflowing.
 //
-// One workgroup per unit of max(d/32, 4) waves.  State wave w (w < d/32) owns
-// state columns [32w, 32w+32) as d/32 MFMA accumulator tiles that stay in
-// registers for the whole segment; at d < 128 the other waves take the Gram
-// tiles and W = Tw K, so the state waves' chain of products is shorter.
+// One workgroup per unit, of one or two teams of max(d/32, 4) waves.  A team
+// takes every chunk (every other one of two teams) through the steps before
+// the state; its state wave w (w < d/32) then advances state columns
+// [32w, 32w+32), d/32 MFMA accumulator tiles.  At d < 128 the other waves take
+// the Gram tiles and W = Tw K, so the state waves' chain of products is shorter.
+// What bounds a unit is this chain of short dependent steps, ten barriers a
+// chunk; two teams (d <= 64, whose LDS holds both) run it for two chunks at
+// once and hand the state from one to the other through the LDS.  One unit of
+// 256 rows at d = 32: 45 us with one team and full products, see launch_scan
+// for when which is taken.
 // Operand precision: K and V arrive rounded once (bf16); beta and the decay
 // factors are folded into T (rounded once) and into Delta (rounded once), so no
 // value is rounded twice.  The state is fp32 throughout.  The two products
@@ -54,19 +60,20 @@ struct ScanCfg {
   static constexpr int CP = kC + PADE;     // pitch of Kt, Vt, Tu, Tw
   static constexpr int R1_KR = kC * KP * EB;
   static constexpr int R1_A = kC * kFP * 4;
-  static constexpr int R1_T2 = 2 * kC * CP * EB;
-  static constexpr int R1 = R1_KR > R1_A ? (R1_KR > R1_T2 ? R1_KR : R1_T2) : (R1_A > R1_T2 ? R1_A : R1_T2);
+  static constexpr int R1 = R1_KR > R1_A ? R1_KR : R1_A;   // K rows, then A, Tu, W
   static constexpr int R2 = D * CP * EB;   // Kt
   static constexpr int R3 = D * CP * EB;   // Vt
-  static constexpr int R4 = kC * kFP * 4;  // T
+  static constexpr int R4 = kC * kFP * 4;  // T, then Tw in its place
   static constexpr int OFF_R2 = R1, OFF_R3 = R1 + R2, OFF_R4 = R1 + R2 + R3;
   static constexpr int OFF_VEC = OFF_R4 + R4;           // 5 x 64 floats
-  static constexpr int LDS = OFF_VEC + 5 * kC * 4;
+  static constexpr int LDS = OFF_VEC + 5 * kC * 4;      // of one team
+  static constexpr int XM = NSW * (D / 32) * 16 * 64 * 4;   // the state on its way between teams
   static constexpr int PIECES = kC * D * EB / 16;       // 16-byte pieces of a chunk
   static constexpr int PER_T = PIECES / THREADS;        // per thread
   static constexpr int VPP = 16 / EB;                   // elements per piece
   static constexpr int PPR = D / VPP;                   // pieces per row
   static_assert(PIECES % THREADS == 0, "chunk split");
+  static_assert(std::is_same<OP, float>::value && CP == kFP && kC * CP * EB <= R1, "Tw takes T's place, Tu A's");
 };
 
 __device__ __forceinline__ bf16x8 pack8(const float* v) {
@@ -173,16 +180,21 @@ __device__ __forceinline__ void store_transposed<float>(char* base, int pitch, i
   p[(col + 3) * pitch + row] = __uint_as_float(v.w);
 }
 
-template <typename OP, int D>
-__global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kernel(ScanArgs a) {
+template <typename OP, int D, int TEAMS>
+__global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kernel(ScanArgs a) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
   using CF = ScanCfg<OP, D>;
   using MF = Mfma<OP>;
   constexpr int NW = CF::NW, NSW = CF::NSW, EB = CF::EB, KP = CF::KP, CP = CF::CP;
   constexpr int NT = D / 32;  // 32-row tiles along d
-  __shared__ __attribute__((aligned(16))) char smem[CF::LDS];
+  constexpr int STEP = TEAMS * kC;     // rows the teams take per round
+  __shared__ __attribute__((aligned(16))) char smem_all[TEAMS * CF::LDS + (TEAMS > 1 ? CF::XM : 0)];
   __shared__ int sel;
 
+  const int lane = threadIdx.x & 63;
+  const int team = TEAMS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / CF::THREADS) : 0;
+  const int tid = threadIdx.x - team * CF::THREADS, wid = tid >> 6;   // within the team
+  char* smem = smem_all + team * CF::LDS;
   char* R1 = smem;
   char* Kt = smem + CF::OFF_R2;
   char* Vt = smem + CF::OFF_R3;
@@ -194,12 +206,10 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
   float* eD = eG + kC;                                        // exp(G_C - G_i)
   float* Am = reinterpret_cast<float*>(R1);                   // A (R1 phase 2)
   char* Tu = R1;                                              // R1 phase 3
-  char* Tw = R1 + kC * CP * EB;
+  char* Tw = reinterpret_cast<char*>(Tm);                     // in T's place
   char* Wr = R1;                                              // R1 phase 4
+  float* XM = reinterpret_cast<float*>(smem_all + TEAMS * CF::LDS) + (size_t)(wid < NSW ? wid : 0) * NT * 16 * 64;
 
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int fr = lane & 31, h2 = lane >> 5;
-  const int fk = h2 * MF::HALF;
   const bool state_wave = NSW == NW || wid < NSW;   // compile-time true when every wave holds state
 
   const int u = blockIdx.x;
@@ -235,7 +245,7 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
     if (st_in && state_wave) {
 #pragma unroll
       for (int r = 0; r < 16; ++r)
-        M[td][r] = st_in[state_base + (size_t)(32 * td + acc_row(r, lane)) * D + 32 * wid + fr];
+        M[td][r] = st_in[state_base + (size_t)(32 * td + acc_row(r, lane)) * D + 32 * wid + (lane & 31)];
     } else {
       M[td] = zero16();
     }
@@ -264,10 +274,18 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
     }
   };
 
-  if (s0 < s1) prefetch(s0);
+  if (s0 < s1) prefetch(s0 + team * kC);
   __syncthreads();
 
-  for (int64_t c0 = s0; c0 < s1; c0 += kC) {
+  // the round's chunks start at r0, this team's at c0 (rows past the segment
+  // are inert; a chunk wholly past it leaves the state alone)
+  for (int64_t r0 = s0; r0 < s1; r0 += STEP) {
+    const int64_t c0 = r0 + team * kC;
+    // opaque per round: the compiler would otherwise keep every fragment's
+    // address in a register across the rounds, and spill
+    int lane_r = lane;
+    asm volatile("" : "+v"(lane_r));
+    const int fr = lane_r & 31, h2 = lane_r >> 5, fk = h2 * MF::HALF;
     // ---- 1. stage the chunk: K row-major (R1) and transposed, V transposed
 #pragma unroll
     for (int i = 0; i < CF::PER_T; ++i) {
@@ -282,7 +300,7 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
       bs[tid] = pb;
     }
     lds_barrier();
-    if (c0 + kC < s1) prefetch(c0 + kC);
+    if (r0 + STEP < s1) prefetch(c0 + STEP);
 
     // ---- 2. in-chunk prefix of log alpha (wave 0); Gram tiles K K^T
     if (wid == 0) {
@@ -325,7 +343,7 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
       const float gj = Gc[j];
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int i = 32 * ti + acc_row(r, lane);
+        const int i = 32 * ti + acc_row(r, lane_r);
         Am[i * kFP + j] = (i > j) ? bs[i] * exp2f(fminf(Gc[i] - gj, 0.f)) * gam[n][r] : 0.f;
       }
     }
@@ -334,7 +352,7 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
     // ---- 4. diagonal 16x16 blocks of T = (I + A)^{-1}: lane = (block, column),
     //         column-sweep forward substitution (16-step dependency chain)
     if (wid == 0) {
-      const int bb = lane >> 4, c = lane & 15;
+      const int bb = lane_r >> 4, c = lane_r & 15;
       const float* Ab = Am + (16 * bb) * kFP + 16 * bb;
       float x[16];
 #pragma unroll
@@ -350,7 +368,7 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
 
     // ---- 5. block rows 1..3: T_bc = -T_bb sum_{m=c}^{b-1} A_bm T_mc (fp32 MFMA)
     {
-      const int i16 = lane & 15, k4 = lane >> 4;
+      const int i16 = lane_r & 15, k4 = lane_r >> 4;
 #pragma unroll
       for (int lv = 1; lv < 4; ++lv) {
         for (int c = wid; c < lv; c += NW) {
@@ -376,7 +394,7 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
       }
     }
 
-    // ---- 6. Tu = T diag(beta), Tw = T diag(beta e^G), rounded once (into R1)
+    // ---- 6. Tu = T diag(beta) (into R1), Tw = T diag(beta e^G) (T's place)
     for (int e = 4 * tid; e < kC * kC; e += 4 * CF::THREADS) {
       const int i = e >> 6, j = e & 63;
       const float4 t = *reinterpret_cast<const float4*>(Tm + i * kFP + j);
@@ -391,7 +409,8 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
 
     // ---- 7. U = Tu V (state waves, their columns); W = Tw K, 2 NT tiles
     //         over the waves past the state waves (over all of them when
-    //         every wave holds state)
+    //         every wave holds state).  T is lower triangular: row tile ti
+    //         needs rows up to 32 (ti + 1) only.
     constexpr int WW0 = NW > NSW ? NSW : 0, NWW = NW - WW0;
     constexpr int WT = (2 * NT + NWW - 1) / NWW;    // W tiles per wave
     f32x16 Uacc[2], Wacc[WT];
@@ -400,11 +419,12 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
       for (int ti = 0; ti < 2; ++ti) {
         Uacc[ti] = zero16();
 #pragma unroll
-        for (int s = 0; s < kC / MF::K; ++s) {
+        for (int s = 0; s < 32 * (ti + 1) / MF::K; ++s) {
           const auto fa = frag_std<OP>(Tu, CP, 32 * ti + fr, s * MF::K + fk);
           const auto fb = frag_std<OP>(Vt, CP, 32 * wid + fr, s * MF::K + fk);
           MF::mma(Uacc[ti], fa, fb);
         }
+        __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
       }
     }
 #pragma unroll
@@ -413,12 +433,17 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
       Wacc[n] = zero16();
       if ((WW0 > 0 && wid < WW0) || q >= 2 * NT) continue;
       const int ti = q / NT, td = q % NT;
+      auto w_steps = [&](int lo) {
 #pragma unroll
-      for (int s = 0; s < kC / MF::K; ++s) {
-        const auto fa = frag_std<OP>(Tw, CP, 32 * ti + fr, s * MF::K + fk);
-        const auto fb = frag_std<OP>(Kt, CP, 32 * td + fr, s * MF::K + fk);
-        MF::mma(Wacc[n], fa, fb);
-      }
+        for (int s = 0; s < 32 / MF::K; ++s) {
+          const auto fa = frag_std<OP>(Tw, CP, 32 * ti + fr, lo + s * MF::K + fk);
+          const auto fb = frag_std<OP>(Kt, CP, 32 * td + fr, lo + s * MF::K + fk);
+          MF::mma(Wacc[n], fa, fb);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
+      };
+      w_steps(0);
+      if (ti) w_steps(32);
     }
     lds_barrier();
 
@@ -429,62 +454,100 @@ __global__ __launch_bounds__(64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kerne
       if ((WW0 > 0 && wid < WW0) || q >= 2 * NT) continue;
       const int ti = q / NT, td = q % NT;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) store_op<OP>(Wr, (32 * ti + acc_row(r, lane)) * KP + 32 * td + fr, Wacc[n][r]);
+      for (int r = 0; r < 16; ++r) store_op<OP>(Wr, (32 * ti + acc_row(r, lane_r)) * KP + 32 * td + fr, Wacc[n][r]);
     }
     lds_barrier();
 
     // ---- 9. Delta = U - W M0 (state from registers), Delta' = e^{G_C - G} Delta
-    if (state_wave) {
-    typename MF::frag dfrag[2][32 / MF::K];
+    auto advance = [&]() {
+      typename MF::frag dfrag[2][32 / MF::K];
 #pragma unroll
-    for (int ti = 0; ti < 2; ++ti) {
-      f32x16 acc = Uacc[ti];
+      for (int ti = 0; ti < 2; ++ti) {
+        f32x16 acc = Uacc[ti];
+#pragma unroll
+        for (int td = 0; td < NT; ++td) {
+#pragma unroll
+          for (int s = 0; s < 32 / MF::K; ++s) {
+            const auto fa = frag_perm<OP>(Wr, KP, 32 * ti + fr, 32 * td, s, h2, true);
+            const auto fb = frag_acc<OP>(M[td], s);
+            MF::mma(acc, fa, fb);
+          }
+          __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] *= eD[32 * ti + acc_row(r, lane_r)];
+#pragma unroll
+        for (int s = 0; s < 32 / MF::K; ++s) dfrag[ti][s] = frag_acc<OP>(acc, s);
+      }
+
+      // ---- 10. M = e^{G_C} M0 + K^T Delta'
+      const float eGC = eG[kC - 1];
 #pragma unroll
       for (int td = 0; td < NT; ++td) {
 #pragma unroll
-        for (int s = 0; s < 32 / MF::K; ++s) {
-          const auto fa = frag_perm<OP>(Wr, KP, 32 * ti + fr, 32 * td, s, h2, true);
-          const auto fb = frag_acc<OP>(M[td], s);
-          MF::mma(acc, fa, fb);
-        }
+        for (int r = 0; r < 16; ++r) M[td][r] *= eGC;
+#pragma unroll
+        for (int ti = 0; ti < 2; ++ti)
+#pragma unroll
+          for (int s = 0; s < 32 / MF::K; ++s) {
+            const auto fa = frag_perm<OP>(Kt, CP, 32 * td + fr, 32 * ti, s, h2, false);
+            MF::mma(M[td], fa, dfrag[ti][s]);
+          }
+        __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
       }
+    };
+    if constexpr (TEAMS == 1) {
+      if (state_wave) advance();
+      lds_barrier();
+    } else {
+      // team after team: the state comes from the team before (the last
+      // round's last for the first) through the LDS, one dword per lane and
+      // register
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] *= eD[32 * ti + acc_row(r, lane)];
+      for (int t = 0; t < TEAMS; ++t) {
+        if (team == t && state_wave && c0 < s1) {
+          if (c0 != s0) {
 #pragma unroll
-      for (int s = 0; s < 32 / MF::K; ++s) dfrag[ti][s] = frag_acc<OP>(acc, s);
-    }
-
-    // ---- 10. M = e^{G_C} M0 + K^T Delta'
-    const float eGC = eG[kC - 1];
+            for (int td = 0; td < NT; ++td)
 #pragma unroll
-    for (int td = 0; td < NT; ++td) {
+              for (int r = 0; r < 16; ++r) M[td][r] = XM[(td * 16 + r) * 64 + lane];
+          }
+          advance();
 #pragma unroll
-      for (int r = 0; r < 16; ++r) M[td][r] *= eGC;
+          for (int td = 0; td < NT; ++td)
 #pragma unroll
-      for (int ti = 0; ti < 2; ++ti)
-#pragma unroll
-        for (int s = 0; s < 32 / MF::K; ++s) {
-          const auto fa = frag_perm<OP>(Kt, CP, 32 * td + fr, 32 * ti, s, h2, false);
-          MF::mma(M[td], fa, dfrag[ti][s]);
+            for (int r = 0; r < 16; ++r) XM[(td * 16 + r) * 64 + lane] = M[td][r];
         }
+        lds_barrier();
+      }
     }
-    }
-    lds_barrier();
   }
 
   if (!state_wave) return;
+  // the team that ran the last chunk (the first one of an empty segment)
+  if (TEAMS > 1 && team != (s1 > s0 ? (int)((s1 - s0 - 1) / kC % TEAMS) : 0)) return;
   float* out = st_out + state_base;
 #pragma unroll
   for (int td = 0; td < NT; ++td)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) out[(size_t)(32 * td + acc_row(r, lane)) * D + 32 * wid + fr] = M[td][r];
+    for (int r = 0; r < 16; ++r) out[(size_t)(32 * td + acc_row(r, lane)) * D + 32 * wid + (lane & 31)] = M[td][r];
 }
 
+// Two teams where every unit has a CU to itself anyway (units beyond that
+// fill the card with one-team workgroups, two per CU, and a second team would
+// only take turns with them).  d = 128 needs most of the LDS for one.
 template <typename OP, int D>
 hipError_t run_scan(const ScanArgs& a, hipStream_t s) {
   const int64_t units = (int64_t)a.n_seg * a.n_layers * a.H_v;
   if (units == 0) return hipSuccess;
-  hipLaunchKernelGGL((gdn_scan_kernel<OP, D>), dim3((unsigned)units), dim3(ScanCfg<OP, D>::THREADS), 0, s, a);
+  constexpr int THREADS = ScanCfg<OP, D>::THREADS;
+  if constexpr (D <= 64) {
+    if (units <= device_cus()) {
+      hipLaunchKernelGGL((gdn_scan_kernel<OP, D, 2>), dim3((unsigned)units), dim3(2 * THREADS), 0, s, a);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((gdn_scan_kernel<OP, D, 1>), dim3((unsigned)units), dim3(THREADS), 0, s, a);
   return hipGetLastError();
 }
 
