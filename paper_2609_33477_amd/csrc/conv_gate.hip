@@ -13,11 +13,13 @@
 // Outputs are head-major ([H][T][d], [H][T]) so the scan reads each 64-row
 // chunk of a head as one contiguous block.
 //
-// tail_kernel (fp32 anchors): per (segment, 64 channels), the q projections
-// of the segment's last w-1 rows as dot products (W_q is used nowhere else),
-// and zeros at positions before the segment's first row (every channel); the
-// k | v channels of existing rows are written with k and v.  With bf16
-// anchors the tail is computed inside the fused projection's grid.
+// tail_block (fp32 anchors): per (segment, 4 channels), the q projections of
+// the segment's last w-1 rows as dot products (W_q is used nowhere else), and
+// zeros at positions before the segment's first row (every channel); the k | v
+// channels of existing rows are written with k and v.  These blocks need
+// nothing the conv computes and ride behind it in one grid (a launch of their
+// own when there are no rows).  With bf16 anchors the tail is computed inside
+// the fused projection's grid.
 #include "sr_device.hpp"
 #include "tail_q.hpp"
 
@@ -43,26 +45,106 @@ __device__ __forceinline__ float silu(float y) { return y / (1.f + expf(-y)); }
 __device__ __forceinline__ float softplus(float x) { return fmaxf(x, 0.f) + log1pf(expf(-fabsf(x))); }
 __device__ __forceinline__ float sigmoid(float x) { return 1.f / (1.f + expf(-x)); }
 
-// One block per (64-row block, head), and one more per row block for the
-// gates.  Rows run in parallel: a wave takes RPW rows of its head at a time
-// (lane = CPL channels of one row), each lane reading the w raw rows its conv
-// needs, so no row waits for the one before it; a key's sum of squares is
-// reduced over the LPH lanes of its row.
-template <typename OUT, typename CW, typename TT, int DH>
-__global__ __launch_bounds__(kConvThreads) void conv_gate_kernel(ConvGateArgs a) {
+// ------------------------------------------------------------------ tail
+constexpr int kTailThreads = 256;
+constexpr int kTailChannels = 4;   // one channel per wave: the channels' loads run in parallel
+
+// 8 consecutive elements starting at element i, as fp32.
+template <typename T>
+__device__ __forceinline__ void load8(const void* p, int64_t i, float* out);
+template <>
+__device__ __forceinline__ void load8<float>(const void* p, int64_t i, float* out) {
+  const float4* q = reinterpret_cast<const float4*>(static_cast<const float*>(p) + i);
+  const float4 x = q[0], y = q[1];
+  out[0] = x.x; out[1] = x.y; out[2] = x.z; out[3] = x.w;
+  out[4] = y.x; out[5] = y.y; out[6] = y.z; out[7] = y.w;
+}
+
+// Channel blocks of the tail per segment
+__host__ __device__ inline int tail_blocks_y(const TailArgs& a) { return (a.c_tail + kTailChannels - 1) / kTailChannels; }
+
+// Block (segment b, channels 4 yb .. + 3); every thread of a kTailThreads block
+template <typename TA, typename TW, typename TT>
+__device__ __forceinline__ void tail_block(const TailArgs& a, int b, int yb) {
+  constexpr int WMAX = 4;
+  const int slot = a.slot_ids ? a.slot_ids[b] : b;
+  if (slot < 0) return;
+  const int64_t s0 = a.cu[b], s1 = a.cu[b + 1];
+  const int w1 = a.w - 1;
+  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+  const int cb = yb * kTailChannels;
+  const int ce = min(a.c_tail, cb + kTailChannels);
+
+  // zero-fill positions that precede the segment's first row
+  for (int idx = tid; idx < (ce - cb) * w1; idx += kTailThreads) {
+    const int c = cb + idx / w1, pos = idx % w1;
+    if (s1 - w1 + pos < s0) Elem<TT>::store(a.tail, ((int64_t)slot * a.c_tail + c) * w1 + pos, 0.f);
+  }
+  if (cb >= a.c_q) return;
+
+  // q channels: dot products of W_q rows with the last w-1 anchor rows
+  const int per_wave = kTailChannels / (kTailThreads / 64);
+  for (int ci = 0; ci < per_wave; ++ci) {
+    const int c = cb + wid * per_wave + ci;
+    if (c >= min(ce, a.c_q)) break;
+    float acc[WMAX - 1] = {0.f, 0.f, 0.f};
+    for (int k = lane * 8; k < a.D; k += 64 * 8) {
+      float wv[8];
+      load8<TW>(a.w_q, (int64_t)c * a.D + k, wv);
+#pragma unroll
+      for (int pos = 0; pos < WMAX - 1; ++pos) {
+        const int64_t t = s1 - w1 + pos;
+        if (pos < w1 && t >= s0) {
+          float xv[8];
+          load8<TA>(a.anchors, t * a.D + k, xv);
+#pragma unroll
+          for (int j = 0; j < 8; ++j) acc[pos] = fmaf(xv[j], wv[j], acc[pos]);
+        }
+      }
+    }
+#pragma unroll
+    for (int pos = 0; pos < WMAX - 1; ++pos)
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) acc[pos] += __shfl_xor(acc[pos], off);
+    if (lane == 0) {
+      const float scale = std::is_same<TW, fp8_t>::value ? Elem<bf16_t>::load(a.s_q, c) : 1.f;
+      for (int pos = 0; pos < w1; ++pos)
+        if (s1 - w1 + pos >= s0)
+          Elem<TT>::store(a.tail, ((int64_t)slot * a.c_tail + c) * w1 + pos, acc[pos] * scale);
+    }
+  }
+}
+
+// One block per (block of ROWS rows, head), one more per row block for the
+// gates, and behind them the tail's blocks (blockIdx.y past n_heads).  Rows
+// run in parallel: a wave takes RPW rows of its head at a time (lane = CPL
+// channels of one row), each lane reading the w raw rows its conv needs, so no
+// row waits for the one before it; a key's sum of squares is reduced over the
+// LPH lanes of its row.
+template <typename OUT, typename CW, typename TT, int DH, int ROWS>
+__global__ __launch_bounds__(kConvThreads) void conv_gate_kernel(ConvGateArgs a, TailArgs tail) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
   constexpr int CPL = DH >= 64 ? DH / 64 : 1;   // channels per lane
   constexpr int LPH = DH / CPL;                   // lanes per head row
   constexpr int RPW = 64 / LPH;                   // rows per wave and pass
   constexpr int WAVES = kConvThreads / 64;
-  constexpr int PASSES = kRowsPerBlock / (WAVES * RPW);
+  constexpr int PASSES = ROWS / (WAVES * RPW);
   constexpr int WMAX = 4;
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int64_t r0 = (int64_t)blockIdx.x * kRowsPerBlock;
-  const int64_t r1 = min(a.T, r0 + kRowsPerBlock);
+  const int64_t r0 = (int64_t)blockIdx.x * ROWS;
+  const int64_t r1 = min(a.T, r0 + ROWS);
   const int n_heads = a.H_k + a.H_v;
   const int C_kv = n_heads * DH;
 
+  if ((int)blockIdx.y > n_heads) {
+    static_assert(kConvThreads == kTailThreads, "tail blocks");
+    if constexpr (std::is_same<OUT, float>::value) {
+      const int64_t i = (int64_t)(blockIdx.y - n_heads - 1) * gridDim.x + blockIdx.x;
+      const int ty = tail_blocks_y(tail);
+      if (i < (int64_t)tail.n_seg * ty) tail_block<float, float, TT>(tail, (int)(i / ty), (int)(i % ty));
+    }
+    return;
+  }
   if ((int)blockIdx.y == n_heads) {
     // ---- gates: thread -> (head, row), rows fastest: ln alpha and beta per row
     const int rows = (int)(r1 - r0);
@@ -140,14 +222,22 @@ __global__ __launch_bounds__(kConvThreads) void conv_gate_kernel(ConvGateArgs a)
   }
 }
 
+// 64 rows per block once those blocks fill the card, else 16: a block's passes
+// over its rows are a chain of memory round trips (256 rows, two heads of 32:
+// 20 blocks of 8 passes 10.3 us, 80 of 2 passes with the tail's blocks 8 us).
 template <typename OUT, typename CW, typename TT, int DH>
-hipError_t run_conv(const ConvGateArgs& a, hipStream_t s) {
+hipError_t run_conv(const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) {
   if (a.T == 0) return hipSuccess;
-  static_assert(kRowsPerBlock % ((kConvThreads / 64) * (64 / (DH / (DH >= 64 ? DH / 64 : 1)))) == 0, "row passes");
   const int n_heads = a.H_k + a.H_v;
-  dim3 grid((unsigned)((a.T + kRowsPerBlock - 1) / kRowsPerBlock), (unsigned)(n_heads + 1));
-  hipLaunchKernelGGL((conv_gate_kernel<OUT, CW, TT, DH>), grid, dim3(kConvThreads), 0, s, a);
-  return hipGetLastError();
+  auto launch = [&](auto kernel, int rows) {
+    const int64_t gx = (a.T + rows - 1) / rows, tb = (int64_t)tail.n_seg * tail_blocks_y(tail);
+    const dim3 grid((unsigned)gx, (unsigned)(n_heads + 1 + (tb + gx - 1) / gx));
+    hipLaunchKernelGGL(kernel, grid, dim3(kConvThreads), 0, s, a, tail);
+    return hipGetLastError();
+  };
+  if ((a.T + kRowsPerBlock - 1) / kRowsPerBlock * (n_heads + 1) >= 4 * device_cus())
+    return launch(conv_gate_kernel<OUT, CW, TT, DH, kRowsPerBlock>, kRowsPerBlock);
+  return launch(conv_gate_kernel<OUT, CW, TT, DH, 16>, 16);
 }
 
 // Heads whose key and value widths differ (Appendix A: OLMo-Hybrid's
@@ -270,7 +360,7 @@ hipError_t run_conv_rect(const ConvGateArgs& a, hipStream_t s) {
 }
 
 template <typename OUT, typename CW, typename TT>
-hipError_t conv_by_head(int d, const ConvGateArgs& a, hipStream_t s) {
+hipError_t conv_by_head(int d, const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) {
   if (a.d_k != a.d_v) {
     if constexpr (std::is_same<OUT, bf16_t>::value) {
       if (a.d_k == 96 && a.d_v == 192) return run_conv_rect<OUT, CW, TT, 96, 192>(a, s);
@@ -278,92 +368,30 @@ hipError_t conv_by_head(int d, const ConvGateArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   }
   switch (d) {
-    case 32: return run_conv<OUT, CW, TT, 32>(a, s);
-    case 64: return run_conv<OUT, CW, TT, 64>(a, s);
-    case 128: return run_conv<OUT, CW, TT, 128>(a, s);
+    case 32: return run_conv<OUT, CW, TT, 32>(a, tail, s);
+    case 64: return run_conv<OUT, CW, TT, 64>(a, tail, s);
+    case 128: return run_conv<OUT, CW, TT, 128>(a, tail, s);
   }
   return hipErrorInvalidValue;
 }
 
 template <typename OUT, typename CW>
-hipError_t conv_by_tail(int tail_dtype, int d, const ConvGateArgs& a, hipStream_t s) {
-  if (tail_dtype == SR_F32) return conv_by_head<OUT, CW, float>(d, a, s);
-  if (tail_dtype == SR_BF16) return conv_by_head<OUT, CW, bf16_t>(d, a, s);
+hipError_t conv_by_tail(int tail_dtype, int d, const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) {
+  if (tail_dtype == SR_F32) return conv_by_head<OUT, CW, float>(d, a, tail, s);
+  if (tail_dtype == SR_BF16) return conv_by_head<OUT, CW, bf16_t>(d, a, tail, s);
   return hipErrorInvalidValue;
-}
-
-// ------------------------------------------------------------------ tail
-constexpr int kTailThreads = 256;
-constexpr int kTailChannels = 4;   // one channel per wave: the channels' loads run in parallel
-
-// 8 consecutive elements starting at element i, as fp32.
-template <typename T>
-__device__ __forceinline__ void load8(const void* p, int64_t i, float* out);
-template <>
-__device__ __forceinline__ void load8<float>(const void* p, int64_t i, float* out) {
-  const float4* q = reinterpret_cast<const float4*>(static_cast<const float*>(p) + i);
-  const float4 x = q[0], y = q[1];
-  out[0] = x.x; out[1] = x.y; out[2] = x.z; out[3] = x.w;
-  out[4] = y.x; out[5] = y.y; out[6] = y.z; out[7] = y.w;
 }
 
 template <typename TA, typename TW, typename TT>
 __global__ __launch_bounds__(kTailThreads) void tail_kernel(TailArgs a) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
-  constexpr int WMAX = 4;
-  const int b = blockIdx.x;
-  const int slot = a.slot_ids ? a.slot_ids[b] : b;
-  if (slot < 0) return;
-  const int64_t s0 = a.cu[b], s1 = a.cu[b + 1];
-  const int w1 = a.w - 1;
-  const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int cb = blockIdx.y * kTailChannels;
-  const int ce = min(a.c_tail, cb + kTailChannels);
-
-  // zero-fill positions that precede the segment's first row
-  for (int idx = tid; idx < (ce - cb) * w1; idx += kTailThreads) {
-    const int c = cb + idx / w1, pos = idx % w1;
-    if (s1 - w1 + pos < s0) Elem<TT>::store(a.tail, ((int64_t)slot * a.c_tail + c) * w1 + pos, 0.f);
-  }
-  if (cb >= a.c_q) return;
-
-  // q channels: dot products of W_q rows with the last w-1 anchor rows
-  const int per_wave = kTailChannels / (kTailThreads / 64);
-  for (int ci = 0; ci < per_wave; ++ci) {
-    const int c = cb + wid * per_wave + ci;
-    if (c >= min(ce, a.c_q)) break;
-    float acc[WMAX - 1] = {0.f, 0.f, 0.f};
-    for (int k = lane * 8; k < a.D; k += 64 * 8) {
-      float wv[8];
-      load8<TW>(a.w_q, (int64_t)c * a.D + k, wv);
-#pragma unroll
-      for (int pos = 0; pos < WMAX - 1; ++pos) {
-        const int64_t t = s1 - w1 + pos;
-        if (pos < w1 && t >= s0) {
-          float xv[8];
-          load8<TA>(a.anchors, t * a.D + k, xv);
-#pragma unroll
-          for (int j = 0; j < 8; ++j) acc[pos] = fmaf(xv[j], wv[j], acc[pos]);
-        }
-      }
-    }
-#pragma unroll
-    for (int pos = 0; pos < WMAX - 1; ++pos)
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) acc[pos] += __shfl_xor(acc[pos], off);
-    if (lane == 0) {
-      const float scale = std::is_same<TW, fp8_t>::value ? Elem<bf16_t>::load(a.s_q, c) : 1.f;
-      for (int pos = 0; pos < w1; ++pos)
-        if (s1 - w1 + pos >= s0)
-          Elem<TT>::store(a.tail, ((int64_t)slot * a.c_tail + c) * w1 + pos, acc[pos] * scale);
-    }
-  }
+  tail_block<TA, TW, TT>(a, blockIdx.x, blockIdx.y);
 }
 
 template <typename TA, typename TW, typename TT>
 hipError_t run_tail(const TailArgs& a, hipStream_t s) {
   if (a.n_seg == 0 || a.w < 2 || a.c_tail == 0) return hipSuccess;
-  dim3 grid(a.n_seg, (a.c_tail + kTailChannels - 1) / kTailChannels);
+  dim3 grid(a.n_seg, tail_blocks_y(a));
   hipLaunchKernelGGL((tail_kernel<TA, TW, TT>), grid, dim3(kTailThreads), 0, s, a);
   return hipGetLastError();
 }
@@ -387,13 +415,15 @@ __global__ __launch_bounds__(kTqThreads) void tail_q_kernel(TailArgs a) {
 }  // namespace
 
 hipError_t launch_conv_gate(int op_dtype, int conv_dtype, int tail_dtype, int d_head,
-                            const ConvGateArgs& a, hipStream_t s) {
+                            const ConvGateArgs& a, const TailArgs* tail, hipStream_t s) {
+  TailArgs t{};                              // n_seg = 0: no tail blocks
+  if (tail && tail->w >= 2) t = *tail;
   if (op_dtype == SR_F32) {
-    if (conv_dtype == SR_F32) return conv_by_tail<float, float>(tail_dtype, d_head, a, s);
-    if (conv_dtype == SR_BF16) return conv_by_tail<float, bf16_t>(tail_dtype, d_head, a, s);
-  } else if (op_dtype == SR_BF16) {
-    if (conv_dtype == SR_F32) return conv_by_tail<bf16_t, float>(tail_dtype, d_head, a, s);
-    if (conv_dtype == SR_BF16) return conv_by_tail<bf16_t, bf16_t>(tail_dtype, d_head, a, s);
+    if (conv_dtype == SR_F32) return conv_by_tail<float, float>(tail_dtype, d_head, a, t, s);
+    if (conv_dtype == SR_BF16) return conv_by_tail<float, bf16_t>(tail_dtype, d_head, a, t, s);
+  } else if (op_dtype == SR_BF16 && t.n_seg == 0) {
+    if (conv_dtype == SR_F32) return conv_by_tail<bf16_t, float>(tail_dtype, d_head, a, t, s);
+    if (conv_dtype == SR_BF16) return conv_by_tail<bf16_t, bf16_t>(tail_dtype, d_head, a, t, s);
   }
   return hipErrorInvalidValue;
 }

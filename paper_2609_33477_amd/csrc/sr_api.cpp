@@ -17,8 +17,9 @@
 //                  the bf16 scan runs as two units of 128
 // fp32 path, and 96 x 192 heads with an odd number of value heads, per layer:
 //     proj_gemm    anchors x [W_k; W_v; W_a; W_b]^T -> P (fp32 workspace)
-//     conv_gate    P -> k_hat, v, log alpha, beta, k | v tail
-//     tail         q part of the conv tail (+ zeros before a segment's start)
+//     conv_gate    P -> k_hat, v, log alpha, beta, k | v tail; on the fp32 path
+//                  blocks behind it write the tail's q part and leading zeros
+//     tail         the same as a launch of its own (96 x 192 heads; no rows)
 // then one state launch per group of <= 32 layers writes the states (the
 // pipelined bf16 scan, the fp32 scan, or the chunked kernel for the unfused
 // 96 x 192 heads).
@@ -307,6 +308,7 @@ sr_status sr_replay_state(const sr_shape* shape, int32_t n_layers, const sr_laye
     t.tail_bf16 = shape->tail_dtype == SR_BF16;
     t.c_tail = c_tail;
     t.err = flag;
+    const bool tail_in_conv = with_tail && !fused && plan.op_dtype == SR_F32 && sr::tail_rides_conv(t, t_total);
     if (fused && (t_total > 0 || with_tail)) {
       // the q-tail blocks ride in the projection's grid (alone when T = 0)
       sr::ProjConvArgs f{};
@@ -384,10 +386,10 @@ sr_status sr_replay_state(const sr_shape* shape, int32_t n_layers, const sr_laye
       c.c_tail = c_tail;
       c.tail_kv_off = c_q;
       c.err = flag;
-      if (timed(SR_KERNEL_CONV_GATE, s, [&] { return sr::launch_conv_gate(plan.op_dtype, shape->conv_dtype, shape->tail_dtype, d, c, s); }) != hipSuccess)
+      if (timed(SR_KERNEL_CONV_GATE, s, [&] { return sr::launch_conv_gate(plan.op_dtype, shape->conv_dtype, shape->tail_dtype, d, c, tail_in_conv ? &t : nullptr, s); }) != hipSuccess)
         return SR_ERR_HIP;
     }
-    if (with_tail && !fused) {
+    if (with_tail && !fused && !tail_in_conv) {
       if (timed(SR_KERNEL_TAIL, s, [&] { return sr::launch_tail(shape->anchor_dtype, shape->weight_dtype, shape->tail_dtype, t, s); }) != hipSuccess)
         return SR_ERR_HIP;
     }

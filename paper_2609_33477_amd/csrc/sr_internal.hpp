@@ -145,11 +145,20 @@ struct ConvGateArgs {
   int32_t d_k, d_v;
 };
 
+// `tail` (fp32 operands, may be null; tail_rides_conv must hold): the conv
+// tail's q part and zeros, as launch_tail would write them, by blocks behind
+// the conv's
 hipError_t launch_conv_gate(int op_dtype, int conv_dtype, int tail_dtype, int d_head,
-                            const ConvGateArgs& a, hipStream_t s);
+                            const ConvGateArgs& a, const TailArgs* tail, hipStream_t s);
 
-// fp32 anchors: per-segment dot products; bf16 anchors: the q-tail blocks on
-// their own (the fused projection's grid carries them when it runs)
+// There are rows, and the tail's blocks (n_seg x 4-channel groups) fit behind
+// the conv's row blocks in a grid of 65535 rows (at most 257 of them the conv's)
+inline bool tail_rides_conv(const TailArgs& a, int64_t T) {
+  return T > 0 && (int64_t)a.n_seg * ((a.c_tail + 3) / 4) <= 60000 * ((T + 63) / 64);
+}
+// fp32 anchors: per-segment dot products (without rows; with them the conv's
+// grid carries these blocks); bf16 anchors: the q-tail blocks on their own
+// (the fused projection's grid carries them when it runs)
 hipError_t launch_tail(int anchor_dtype, int weight_dtype, int tail_dtype, const TailArgs& a,
                        hipStream_t s);
 
