@@ -19,7 +19,7 @@
 //     over steps m-6 .. m-4; Tu = T diag(beta) in two bf16 parts and
 //     Tw = T diag(beta 2^G) (m-3); then W^T = K^T Tw^T, which leaves W
 //     row-major (m-2 for sub-chunk m, m-1 for m+1);
-//   d/32 state waves, wave s owning state columns [32s, 32s+32) as 2 d/16
+//   d/32 state waves, wave s owning 16 CC state columns as CC d/16
 //     16x16 fp32 accumulator tiles for the whole unit: at step n they
 //     run the state lines of sub-chunk n from registers (in phases that
 //     pair MFMA groups with the VALU work they do not wait on), then read
@@ -54,6 +54,12 @@
 // W rows hold their columns in the state's k order (32q + 4g .. + 3, then
 // 32q + 16 + 4g .. + 3, at 32q + 8g) so each fragment is one 16-byte read,
 // with the row pitch 8 mod 64 dwords measured conflict free for those.
+//
+// Few units (CC = 1).  A unit is one serial chain of steps whose pace the state
+// waves set (CC = 2: ~2.8K cycles, prep phases ~2.0K).  Where twice the units
+// still have a CU each, a unit's state columns go to two workgroups of half
+// of them, each with its own prep: the state step halves and the prep sets the
+// pace.
 //
 // Rectangular heads (SPLIT, d = 128): OLMo-Hybrid's 192-wide value heads
 // arrive as two 96-column halves and its 96-wide keys as 128-column rows,
@@ -191,11 +197,15 @@ __device__ __forceinline__ int kv_off(int r, int cb, int h) {
 }
 
 // SPLIT: value heads run as several units (the v_split fields of ScanArgs);
-// the square-head kernels are built without it.
-template <int D, bool SPLIT>
+// the square-head kernels are built without it.  CC: 16-column tiles per state
+// wave; with 1 a workgroup runs one unit's half of the state columns and the
+// grid holds both halves of every unit.
+template <int D, bool SPLIT, int CC>
 __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(ScanArgs a) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
   using CF = Cfg<D>;
+  constexpr int SUBS = 2 / CC;                     // workgroups per unit
+  static_assert(!(SPLIT && SUBS > 1), "column halves are for square heads");
   constexpr int NSW = CF::NSW, NP = CF::NP, NT = CF::NT, WP = CF::WP, NK = CF::NK, NV = CF::NV, QG = CF::QG;
   __shared__ __attribute__((aligned(16))) char smem[CF::LDS];
   __shared__ int seg_of[kSortMax];                 // rank -> segment, longest first
@@ -224,8 +234,13 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
   // 2i + 1, which share a key head when H_v = 2 H_k, so its K rows are
   // fetched into one L2.
   const int units = a.n_seg * a.n_layers * a.H_v;
-  const int G = gridDim.x, bid = blockIdx.x;
-  const int pi = (G & 15) == 0 ? (bid & ~15) + 2 * (bid & 7) + ((bid >> 3) & 1) : bid;
+  const int G = gridDim.x / SUBS;
+  const int bid0 = blockIdx.x;
+  // SUBS = 2: blocks b and b + 8 of each 16 (one XCD) are the halves of a unit
+  const int half = SUBS > 1 ? (bid0 >> 3) & 1 : 0;
+  const int bid = SUBS > 1 ? (bid0 >> 4) * 8 + (bid0 & 7) : bid0;
+  if (SUBS > 1 && bid >= units) return;
+  const int pi = SUBS > 1 ? bid : (G & 15) == 0 ? (bid & ~15) + 2 * (bid & 7) + ((bid >> 3) & 1) : bid;
   if (a.n_seg <= kSortMax) {
     for (int sg = tid; sg < a.n_seg; sg += CF::THREADS) {
       const int sl = a.slot_ids ? a.slot_ids[sg] : sg;
@@ -303,8 +318,9 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
     const float* si = st_in_of(layer);
     const size_t ib = state_base(u_slot[k], head);
     float* so = st_out_of(layer) + ib;
-    for (int i = tid; i < srows * scols; i += CF::THREADS) {
-      const size_t o = (size_t)(i / scols) * spitch + i % scols;
+    const int cols = SUBS > 1 ? D / SUBS : scols;
+    for (int i = tid; i < srows * cols; i += CF::THREADS) {
+      const size_t o = (size_t)(i / cols) * spitch + half * cols + i % cols;
       so[o] = si ? si[ib + o] : 0.f;
     }
   }
@@ -708,15 +724,16 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
   }
 
   // ================================================================== state
-  // tile (td, cc) holds M[16 td + 4g + r][32 sw + 16 cc + li]
+  // tile (td, cc) holds M[16 td + 4g + r][col0 + 16 cc + li]
   const int sw = wid - NP;
-  f32x4 M[NT][2];
+  const int col0 = half * (D / 2) + 16 * CC * sw;   // half is 0 with CC = 2
+  f32x4 M[NT][CC];
 
   // The operands of a state step, read one step ahead: during step n the
   // wave issues the MFMAs of sub-chunk n from registers, then reads
   // sub-chunk n+1's operands, whose latency overlaps those MFMAs and the
   // barrier.
-  bf16x8 t0, t1, t0l, t1l, vf[2], wf[NT / 2][2], kt[NT];
+  bf16x8 t0, t1, t0l, t1l, vf[CC], wf[NT / 2][2], kt[NT];
   float4 e0, e1;
   float decay;
   auto load_ops = [&](int m) {
@@ -730,7 +747,7 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
     t0l = tr_pair(Tu + CF::SZ_TT + tr_t, kTP * 2, false);
     t1l = tr_pair(Tu + CF::SZ_TT + tr_t + 16 * 2, kTP * 2, false);
 #pragma unroll
-    for (int cc = 0; cc < 2; ++cc) vf[cc] = tr_kv(Vc, 2 * sw + cc);
+    for (int cc = 0; cc < CC; ++cc) vf[cc] = tr_kv(Vc, col0 / 16 + cc);
     // W rows 16 bi + li in the state's k order (stored that way)
 #pragma unroll
     for (int q = 0; q < NT / 2; ++q)
@@ -742,7 +759,7 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
 #pragma unroll
     for (int td = 0; td < NT; ++td) kt[td] = tr_kv(Kc, td);
   };
-  // The state lines of a sub-chunk for this wave's 32 columns, in six phases
+  // The state lines of a sub-chunk for this wave's columns (CC = 2), in six phases
   // that pair each group of MFMAs with VALU work it does not wait on: the
   // two column tiles cc run one after the other, so the bf16 copies of the
   // state, its decay and the scaled Delta of one tile are formed under the
@@ -750,8 +767,8 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
   // order as a plain loop would give them, so the results do not depend on
   // this schedule.
   auto state_step = [&]() {
-    f32x4 dl[2][2];
-    bf16x8 mb[NT / 2], dfr[2];
+    f32x4 dl[2][CC];
+    bf16x8 mb[NT / 2], dfr[CC];
     // U = Tu V for row halves bi of column tile cc (the bf16 copy of M0's
     // tile cc made under those products)
     auto u_and_copy = [&](int cc) {
@@ -800,6 +817,15 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
       }
       __builtin_amdgcn_sched_barrier(0);
     };
+    if constexpr (CC == 1) {
+      u_and_copy(0);
+      wm(0);
+      decay_tile(0, 0, NT);
+      pair_groups();
+      scale_delta(0);
+      update(0);
+      return;
+    } else {
     u_and_copy(0);                       // 1: U of tile 0 | bf16 copy of M0's tile 0
     wm(0);                               // 2: (-W) M0 into tile 0 | decay of M's tile 0
     decay_tile(0, 0, NT);
@@ -814,6 +840,7 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
     scale_delta(1);
     pair_groups();
     update(1);                           // 6: M += K^T Delta for tile 1
+    }
   };
 
   // ---- steps -9 .. NSC-1: the state lines of sub-chunk n, then the reads
@@ -822,11 +849,11 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
   // state) and is stored after its last one.
   Cursor cs = cursor_new();   // unit of sub-chunk n
   auto unit_base = [&](const Cursor& c) {
-    return state_base(uni(u_slot[c.k]), uni(u_lh[c.k]) % a.H_v) + (size_t)(4 * g) * spitch + 32 * sw + li;
+    return state_base(uni(u_slot[c.k]), uni(u_lh[c.k]) % a.H_v) + (size_t)(4 * g) * spitch + col0 + li;
   };
   // this lane's state element (16 td + r, 16 cc) of the wave's columns lies
   // inside the unit's rows and columns
-  auto in_state = [&](int td, int cc, int r) { return 4 * g + 16 * td + r < srows && 32 * sw + li + 16 * cc < scols; };
+  auto in_state = [&](int td, int cc, int r) { return 4 * g + 16 * td + r < srows && col0 + li + 16 * cc < scols; };
   for (int n = -9; n < NSC; ++n) {
     if (n >= 0) {
       if (n >= cs.end) (void)sub(n, cs);
@@ -836,7 +863,7 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
 #pragma unroll
         for (int td = 0; td < NT; ++td)
 #pragma unroll
-          for (int cc = 0; cc < 2; ++cc)
+          for (int cc = 0; cc < CC; ++cc)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
               M[td][cc][r] = si && in_state(td, cc, r) ? si[base + (size_t)(16 * td + r) * spitch + 16 * cc] : 0.f;
@@ -847,7 +874,7 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
 #pragma unroll
         for (int td = 0; td < NT; ++td)
 #pragma unroll
-          for (int cc = 0; cc < 2; ++cc)
+          for (int cc = 0; cc < CC; ++cc)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
               if (in_state(td, cc, r)) out[(size_t)(16 * td + r) * spitch + 16 * cc] = M[td][cc][r];
@@ -862,11 +889,22 @@ template <int D, bool SPLIT = false>
 hipError_t run(const ScanArgs& a, hipStream_t s) {
   const int64_t units = (int64_t)a.n_seg * a.n_layers * a.H_v;
   if (units == 0) return hipSuccess;
+  // Twice the units on a CU each: two workgroups per unit.  Blocks come in
+  // groups of 16, 8 units' halves.  Measured (us, one workgroup per unit /
+  // two): 16 units of 64 sub-chunks 77.9 / 73.2, 96 of 4 17.9 / 15.5 (the prep
+  // phases set the pace then)
+  if constexpr (!SPLIT) {
+    const int64_t halves = (units + 7) / 8 * 16;
+    if (halves <= device_cus()) {
+      hipLaunchKernelGGL((gdn_scan_bf16_kernel<D, false, 1>), dim3((unsigned)halves), dim3(Cfg<D>::THREADS), 0, s, a);
+      return hipGetLastError();
+    }
+  }
   // one workgroup per CU (one fits), each running its share of the units back to back
   // (at most kScanUnits)
   int64_t grid = units < device_cus() ? units : device_cus();
   if (grid * kScanUnits < units) grid = (units + kScanUnits - 1) / kScanUnits;
-  hipLaunchKernelGGL((gdn_scan_bf16_kernel<D, SPLIT>), dim3((unsigned)grid), dim3(Cfg<D>::THREADS), 0, s, a);
+  hipLaunchKernelGGL((gdn_scan_bf16_kernel<D, SPLIT, 2>), dim3((unsigned)grid), dim3(Cfg<D>::THREADS), 0, s, a);
   return hipGetLastError();
 }
 
