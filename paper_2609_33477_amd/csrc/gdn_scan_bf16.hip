@@ -55,11 +55,11 @@
 // 32q + 16 + 4g .. + 3, at 32q + 8g) so each fragment is one 16-byte read,
 // with the row pitch 8 mod 64 dwords measured conflict free for those.
 //
-// Few units (CC = 1).  A unit is one serial chain of steps whose pace the state
-// waves set (CC = 2: ~2.8K cycles, prep phases ~2.0K).  Where twice the units
-// still have a CU each, a unit's state columns go to two workgroups of half
-// of them, each with its own prep: the state step halves and the prep sets the
-// pace.
+// Few units (CC = 1).  A unit is one serial chain of steps.  Where twice the
+// units still have a CU each, a unit's state columns go to two workgroups of
+// half of them, each with its own prep.  Halving the state step takes only 6
+// to 13% off the chain (figures in run()), so the rest, the prep among it,
+// bounds it then.
 //
 // Rectangular heads (SPLIT, d = 128): OLMo-Hybrid's 192-wide value heads
 // arrive as two 96-column halves and its 96-wide keys as 128-column rows,
@@ -826,20 +826,20 @@ __global__ __launch_bounds__(64 * (D / 32 + 4), 1) void gdn_scan_bf16_kernel(Sca
       update(0);
       return;
     } else {
-    u_and_copy(0);                       // 1: U of tile 0 | bf16 copy of M0's tile 0
-    wm(0);                               // 2: (-W) M0 into tile 0 | decay of M's tile 0
-    decay_tile(0, 0, NT);
-    pair_groups();
-    u_and_copy(1);                       // 3: U of tile 1 | bf16 copy of M0's tile 1
-    wm(1);                               // 4: (-W) M0 into tile 1 | scaled Delta of tile 0, half the decay of tile 1
-    scale_delta(0);
-    decay_tile(1, 0, NT / 2);
-    pair_groups();
-    update(0);                           // 5: M += K^T Delta for tile 0 | the rest, scaled Delta of tile 1
-    decay_tile(1, NT / 2, NT);
-    scale_delta(1);
-    pair_groups();
-    update(1);                           // 6: M += K^T Delta for tile 1
+      u_and_copy(0);                       // 1: U of tile 0 | bf16 copy of M0's tile 0
+      wm(0);                               // 2: (-W) M0 into tile 0 | decay of M's tile 0
+      decay_tile(0, 0, NT);
+      pair_groups();
+      u_and_copy(1);                       // 3: U of tile 1 | bf16 copy of M0's tile 1
+      wm(1);                               // 4: (-W) M0 into tile 1 | scaled Delta of tile 0, half the decay of tile 1
+      scale_delta(0);
+      decay_tile(1, 0, NT / 2);
+      pair_groups();
+      update(0);                           // 5: M += K^T Delta for tile 0 | the rest, scaled Delta of tile 1
+      decay_tile(1, NT / 2, NT);
+      scale_delta(1);
+      pair_groups();
+      update(1);                           // 6: M += K^T Delta for tile 1
     }
   };
 
@@ -891,8 +891,9 @@ hipError_t run(const ScanArgs& a, hipStream_t s) {
   if (units == 0) return hipSuccess;
   // Twice the units on a CU each: two workgroups per unit.  Blocks come in
   // groups of 16, 8 units' halves.  Measured (us, one workgroup per unit /
-  // two): 16 units of 64 sub-chunks 77.9 / 73.2, 96 of 4 17.9 / 15.5 (the prep
-  // phases set the pace then)
+  // two, medians of 6): 16 units of 64 sub-chunks 77.9 / 73.2, 96 of 4
+  // 17.9 / 15.5.  Beyond that a unit's halves would share a CU's turn with
+  // another unit's, each doing the unit's whole prep again.
   if constexpr (!SPLIT) {
     const int64_t halves = (units + 7) / 8 * 16;
     if (halves <= device_cus()) {

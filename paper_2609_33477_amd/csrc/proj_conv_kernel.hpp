@@ -185,16 +185,12 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
   auto layer_args = [&](int l) -> const ProjConvArgs& {
     return *reinterpret_cast<const ProjConvArgs*>(kargs + offsetof(ProjConvBatch, layer) + l * sizeof(ProjConvArgs));
   };
-  // Non-zero: the call's table check failed and the block writes nothing.  A
-  // tile looks at it only once its sources are set up (reading them is safe
-  // either way), so the load's latency hides under that.
-  const int bad = *pb.layer[0].err;
+  if (pb.layer[0].err && *pb.layer[0].err) return;   // the call's table check failed: write nothing
   constexpr bool FP8 = std::is_same<TB, fp8_t>::value;
   __shared__ __attribute__((aligned(1024))) char smem_raw[kTileLds<C>];
   constexpr int MI = C::MI, U = 4 * MI;    // accumulator blocks and rows per lane
   const int n_tiles = pb.n_layers * tiles_m * tiles_n;
   if ((int)blockIdx.x >= n_tiles) {
-    if (bad) return;
     const int b = (int)blockIdx.x - n_tiles;
     int l = 0;
     while (l + 1 < pb.n_layers && b >= pb.tq_off[l + 1]) ++l;
@@ -256,7 +252,6 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
           p = static_cast<const char*>(a.seg[s].ptr) + (int64_t)(n - a.seg[s].n0) * K * Elem<TB>::bytes;
       b_ptr[i] = p + tile_b_chunk<TB>(row, lane) * 16;
     }
-    if (bad) return;
     const int n_wave = a.N - (n0 + wn * 128);        // valid columns of this wave's 128
     const int KT = K / kTileK;
     if (n_wave > 64) tile_main_loop<C, TB, 8>(acc, a_base, a_off, b_ptr, KT, smem_raw, wid, lane);
