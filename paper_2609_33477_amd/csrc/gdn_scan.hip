@@ -76,22 +76,9 @@ struct ScanCfg {
   static_assert(std::is_same<OP, float>::value && CP == kFP && kC * CP * EB <= R1, "Tw takes T's place, Tu A's");
 };
 
-__device__ __forceinline__ bf16x8 pack8(const float* v) {
-  uint4 u;
-  u.x = f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-  u.y = f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-  u.z = f32_to_bf16_bits(v[4]) | ((uint32_t)f32_to_bf16_bits(v[5]) << 16);
-  u.w = f32_to_bf16_bits(v[6]) | ((uint32_t)f32_to_bf16_bits(v[7]) << 16);
-  return as_bf16x8(u);
-}
-
 // Standard-order operand fragment from a row-major LDS matrix.
 template <typename OP>
 __device__ __forceinline__ typename Mfma<OP>::frag frag_std(const char* base, int pitch, int row, int k);
-template <>
-__device__ __forceinline__ bf16x8 frag_std<bf16_t>(const char* base, int pitch, int row, int k) {
-  return as_bf16x8(*reinterpret_cast<const uint4*>(base + ((size_t)row * pitch + k) * 2));
-}
 template <>
 __device__ __forceinline__ float frag_std<float>(const char* base, int pitch, int row, int k) {
   return *reinterpret_cast<const float*>(base + ((size_t)row * pitch + k) * 4);
@@ -103,16 +90,6 @@ template <typename OP>
 __device__ __forceinline__ typename Mfma<OP>::frag frag_perm(const char* base, int pitch, int row, int col0,
                                                               int s, int h, bool negate);
 template <>
-__device__ __forceinline__ bf16x8 frag_perm<bf16_t>(const char* base, int pitch, int row, int col0, int s,
-                                                     int h, bool negate) {
-  const char* p = base + ((size_t)row * pitch + col0 + 16 * s + 4 * h) * 2;
-  const uint2 lo = *reinterpret_cast<const uint2*>(p);
-  const uint2 hi = *reinterpret_cast<const uint2*>(p + 16);
-  uint4 u = make_uint4(lo.x, lo.y, hi.x, hi.y);
-  if (negate) { u.x ^= 0x80008000u; u.y ^= 0x80008000u; u.z ^= 0x80008000u; u.w ^= 0x80008000u; }
-  return as_bf16x8(u);
-}
-template <>
 __device__ __forceinline__ float frag_perm<float>(const char* base, int pitch, int row, int col0, int s, int h,
                                                   bool negate) {
   const float v = *reinterpret_cast<const float*>(base + ((size_t)row * pitch + col0 + 8 * (s >> 2) + 4 * h + (s & 3)) * 4);
@@ -123,21 +100,10 @@ __device__ __forceinline__ float frag_perm<float>(const char* base, int pitch, i
 template <typename OP>
 __device__ __forceinline__ typename Mfma<OP>::frag frag_acc(const f32x16& acc, int s);
 template <>
-__device__ __forceinline__ bf16x8 frag_acc<bf16_t>(const f32x16& acc, int s) {
-  float v[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) v[q] = acc[8 * s + q];
-  return pack8(v);
-}
-template <>
 __device__ __forceinline__ float frag_acc<float>(const f32x16& acc, int s) { return acc[s]; }
 
 template <typename OP>
 __device__ __forceinline__ void store_op(char* base, int idx, float v);
-template <>
-__device__ __forceinline__ void store_op<bf16_t>(char* base, int idx, float v) {
-  reinterpret_cast<uint16_t*>(base)[idx] = f32_to_bf16_bits(v);
-}
 template <>
 __device__ __forceinline__ void store_op<float>(char* base, int idx, float v) {
   reinterpret_cast<float*>(base)[idx] = v;
@@ -147,13 +113,6 @@ __device__ __forceinline__ void store_op<float>(char* base, int idx, float v) {
 template <typename OP>
 __device__ __forceinline__ void store4_op(char* base, int idx, const float* v);
 template <>
-__device__ __forceinline__ void store4_op<bf16_t>(char* base, int idx, const float* v) {
-  uint2 u;
-  u.x = f32_to_bf16_bits(v[0]) | ((uint32_t)f32_to_bf16_bits(v[1]) << 16);
-  u.y = f32_to_bf16_bits(v[2]) | ((uint32_t)f32_to_bf16_bits(v[3]) << 16);
-  *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(base) + idx) = u;
-}
-template <>
 __device__ __forceinline__ void store4_op<float>(char* base, int idx, const float* v) {
   *reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + idx) = make_float4(v[0], v[1], v[2], v[3]);
 }
@@ -161,16 +120,6 @@ __device__ __forceinline__ void store4_op<float>(char* base, int idx, const floa
 // Scatter a 16-byte piece (VPP elements of one row) into a transposed matrix.
 template <typename OP>
 __device__ __forceinline__ void store_transposed(char* base, int pitch, int col, int row, const uint4& v);
-template <>
-__device__ __forceinline__ void store_transposed<bf16_t>(char* base, int pitch, int col, int row, const uint4& v) {
-  uint16_t* p = reinterpret_cast<uint16_t*>(base);
-  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    p[(col + 2 * e) * pitch + row] = (uint16_t)(w[e] & 0xffffu);
-    p[(col + 2 * e + 1) * pitch + row] = (uint16_t)(w[e] >> 16);
-  }
-}
 template <>
 __device__ __forceinline__ void store_transposed<float>(char* base, int pitch, int col, int row, const uint4& v) {
   float* p = reinterpret_cast<float*>(base);

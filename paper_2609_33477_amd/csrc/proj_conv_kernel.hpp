@@ -109,10 +109,9 @@ __device__ __forceinline__ void bfly_step(float* s, int lc) {
   }
 }
 
-// OR / AND of a 32-bit value over the 64 lanes (the result is wave-uniform)
-template <bool OR>
-__device__ __forceinline__ uint32_t wave_reduce(uint32_t v) {
-  auto op = [](uint32_t x, int y) { return OR ? x | (uint32_t)y : x & (uint32_t)y; };
+// OR of a 32-bit value over the 64 lanes (the result is wave-uniform)
+__device__ __forceinline__ uint32_t wave_or(uint32_t v) {
+  auto op = [](uint32_t x, int y) { return x | (uint32_t)y; };
   v = op(v, __builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false));    // lane ^ 1
   v = op(v, __builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false));    // lane ^ 2
   v = op(v, __builtin_amdgcn_mov_dpp((int)v, 0x124, 0xF, 0xF, false));   // quad g -/+ 1
@@ -353,7 +352,7 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
   }
   if (a.tail == nullptr) tailm = 0u;
   const bool tail_bf16 = a.tail_bf16 != 0;
-  const uint32_t tail_rows = wave_fast ? 0u : wave_reduce<true>(tailm);   // rows some lane keeps for the tail
+  const uint32_t tail_rows = wave_fast ? 0u : wave_or(tailm);   // rows some lane keeps for the tail
 
   static_for<NH>([&](auto hd_c) {
     constexpr int hd = decltype(hd_c)::value;

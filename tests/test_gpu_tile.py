@@ -8,7 +8,7 @@ once to bf16, 5e-3 per slab."""
 import pytest
 
 import workloads as W
-from gpu_harness import TOL_BF16, check_pairs, log, run, upload
+from gpu_harness import TOL_BF16, TOL_F32, check_pairs, log, run, upload
 from test_gpu_group import _check_group, _run
 from workloads.device import upload_group
 from workloads.group import make_group
@@ -61,6 +61,26 @@ def test_states_do_not_depend_on_the_tile_shape():
         run(part)
         assert torch.equal(part.layers[0].state_out[0], dev.layers[0].state_out[b]), b
         assert torch.equal(part.layers[0].tail_out[0], dev.layers[0].tail_out[b]), b
+
+
+def _f32_shape(d_model, heads, d):
+    return W.Shape(d_model, heads, heads, d, d, anchor_dtype=W.F32, weight_dtype=W.F32, conv_dtype=W.F32,
+                   tail_dtype=W.F32)
+
+
+# fp32 scan: lengths around its 64-row chunks, where two teams take turns at the
+# state (none, one, an odd and an even number of chunks), and enough units for
+# one team each.  With the many heads the conv takes its 64-row blocks, with the
+# few 16-row ones; the tail's blocks ride behind both.
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("heads,layers,lens", [(2, 1, [1, 64, 65, 128, 129, 200]), (2, 1, [3, 0, 192]), (2, 2, [2]),
+                                               (64, 1, [1, 64, 65, 128, 129, 200, 66])])
+def test_f32_scan_and_conv_edges(heads, layers, lens, d):
+    wl = W.make_workload("f32", _f32_shape(64, heads, d), lens, n_layers=layers, seed=d + heads)
+    log(f"fp32 edges: {lens}, {heads} heads of {d}, {layers} layers")
+    dev = upload(wl)
+    run(dev)
+    check_pairs(dev, [(li, b) for li in range(layers) for b in range(len(lens))], TOL_F32)
 
 
 @pytest.mark.parametrize("rows,d_ff", [(256, 128), (257, 192 + 64), (510, 384)])
