@@ -73,7 +73,10 @@ __device__ __forceinline__ uint4 tile_ld16(const tile_lds* p) {
 // Per tile shape and B storage.  ROW: bytes of a B row per K-step; DA, DB: 1 KB
 // DMA blocks per wave and K-step; NA, NB: K-steps of A and B in flight or in
 // use, refilled slot by slot (SHARED: one ring of five slots for both, A three
-// and B two steps ahead); SPACING: MFMAs per refill; PENDING: DMAs that may
+// and B two steps ahead); BARRIER, SPACING: MFMAs before the hand-over and per
+// refill (fp8 has six refills a step against eight: 24 and 6 against 28 and 5
+// 12958 against 13131 us for 12 layers of 16384 rows, D 5120, N 8288; 20 and 7
+// 12980, 16 and 8 13151; bf16 takes 1% longer with 24); PENDING: DMAs that may
 // still be in flight at a hand-over once the next step has landed (issue order
 // of a step: B, then A); PENDING0: the same before the first step.
 template <typename C, typename TB>
@@ -81,14 +84,15 @@ struct TileRing {
   static constexpr bool FP8 = std::is_same<TB, fp8_t>::value, SHARED = !FP8;
   static constexpr int ROW = FP8 ? 64 : 128, DA = 4, DB = FP8 ? 2 : 4;
   static constexpr int NA = 3, NB = FP8 ? 4 : 2;
-  static constexpr int SPACING = C::MI == 4 ? (FP8 ? 5 : 4) : (FP8 ? 3 : 2);
+  static constexpr int BARRIER = FP8 && C::MI == 4 ? 24 : C::BARRIER;
+  static constexpr int SPACING = C::MI == 4 ? (FP8 ? 6 : 4) : (FP8 ? 3 : 2);
   static constexpr int PENDING = SHARED ? DA : (NA - 2) * (DA + DB);
   static constexpr int PENDING0 = (NA - 1) * DA + (NB - 1) * DB;
   static constexpr int TAIL = NA > NB ? NA : NB;   // last steps, whose refills would lie past K
   static constexpr int BSTEP = C::ROWS * ROW;      // bytes of one K-step of B
   static_assert(C::ROWS * 128 == DA * C::WAVES * 1024 && BSTEP == DB * C::WAVES * 1024, "DMA split");
   static_assert(NA * kTileHalf<C> + NB * BSTEP <= kTileLds<C>, "LDS");
-  static_assert((DA + DB) * SPACING <= 16 * C::MI - C::BARRIER, "the refills fit behind the hand-over");
+  static_assert((DA + DB) * SPACING <= 16 * C::MI - BARRIER, "the refills fit behind the hand-over");
   // DMAs that may be in flight when `t` steps remain (t <= TAIL)
   static constexpr int pending(int t) {
     if (SHARED) return t >= 3 ? DA : 0;
@@ -316,7 +320,7 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[C::MI][8], const cha
       if (q % C::RD == 0) read_half(sa, sb, 1, q / C::RD);   // second-half fragments of this step
       convert(0, q);
       __builtin_amdgcn_sched_barrier(0);
-      if (q == C::BARRIER - 1 && !LAST) {
+      if (q == R::BARRIER - 1 && !LAST) {
         // this wave's reads of the step's slots are complete and its DMAs of
         // the next step have landed; after the barrier so have every wave's
         wait_vm<W>();
@@ -324,8 +328,8 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[C::MI][8], const cha
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
       }
-      if (q >= C::BARRIER) {
-        refill(q - C::BARRIER);
+      if (q >= R::BARRIER) {
+        refill(q - R::BARRIER);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
@@ -337,7 +341,7 @@ __device__ __forceinline__ void tile_main_loop(f32x4 (&acc)[C::MI][8], const cha
         if (FP8 && q % MI == 0) read_b(nb, 0, q / MI);  // raw[j] was converted for the last time in group j - 2
       }
       convert(1, q);
-      refill(q + Q - C::BARRIER);
+      refill(q + Q - R::BARRIER);
       __builtin_amdgcn_sched_barrier(0);
     }
     sa = na;
