@@ -26,7 +26,7 @@
 // once and hand the state from one to the other through the LDS.  One unit of
 // 256 rows at d = 32: 45 us with one team and full products, see launch_scan
 // for when which is taken.
-// Operand precision: K and V arrive rounded once (bf16); beta and the decay
+// Operand precision: everything is fp32, K and V as they arrive; beta and the decay
 // factors are folded into T (rounded once) and into Delta (rounded once), so no
 // value is rounded twice.  The state is fp32 throughout.  The two products
 // that touch the state (W M0 and K^T Delta') take the state / Delta operand
@@ -482,21 +482,25 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
     for (int r = 0; r < 16; ++r) out[(size_t)(32 * td + acc_row(r, lane)) * D + 32 * wid + (lane & 31)] = M[td][r];
 }
 
-// Two teams where every unit has a CU to itself anyway (units beyond that
-// fill the card with one-team workgroups, two per CU, and a second team would
-// only take turns with them).  d = 128 needs most of the LDS for one.
+// Teams per unit.  d = 64: always two, a CU holds one workgroup of either kind.
+// d = 32: two while every unit has a CU to itself; beyond that two one-team
+// workgroups share a CU and a second team would only take turns with them.
+// d = 128 needs most of the LDS for one.  256 CUs, 1024 rows a unit (us, one
+// team / two): d = 32, 256 units 161 / 131, 272 units 201 / 256, 1024 units
+// 412 / 530; d = 64, 256 units 247 / 209, 272 units 486 / 407, 1024 units
+// 994 / 848.
 template <typename OP, int D>
 hipError_t run_scan(const ScanArgs& a, hipStream_t s) {
   const int64_t units = (int64_t)a.n_seg * a.n_layers * a.H_v;
   if (units == 0) return hipSuccess;
   constexpr int THREADS = ScanCfg<OP, D>::THREADS;
   if constexpr (D <= 64) {
-    if (units <= device_cus()) {
+    if (D == 64 || units <= device_cus()) {
       hipLaunchKernelGGL((gdn_scan_kernel<OP, D, 2>), dim3((unsigned)units), dim3(2 * THREADS), 0, s, a);
       return hipGetLastError();
     }
   }
-  hipLaunchKernelGGL((gdn_scan_kernel<OP, D, 1>), dim3((unsigned)units), dim3(THREADS), 0, s, a);
+  if constexpr (D != 64) hipLaunchKernelGGL((gdn_scan_kernel<OP, D, 1>), dim3((unsigned)units), dim3(THREADS), 0, s, a);
   return hipGetLastError();
 }
 

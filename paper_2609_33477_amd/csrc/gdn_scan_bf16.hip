@@ -57,7 +57,7 @@
 //
 // Few units (CC = 1).  A unit is one serial chain of steps.  Where twice the
 // units still have a CU each, a unit's state columns go to two workgroups of
-// half of them, each with its own prep.  Halving the state step takes only 6
+// half of them, each with its own prep.  Halving the state step takes only 5
 // to 13% off the chain (figures in run()), so the rest, the prep among it,
 // bounds it then.
 //
@@ -891,9 +891,9 @@ hipError_t run(const ScanArgs& a, hipStream_t s) {
   if (units == 0) return hipSuccess;
   // Twice the units on a CU each: two workgroups per unit.  Blocks come in
   // groups of 16, 8 units' halves.  Measured (us, one workgroup per unit /
-  // two, medians of 6): 16 units of 64 sub-chunks 77.9 / 73.2, 96 of 4
-  // 17.9 / 15.5.  Beyond that a unit's halves would share a CU's turn with
-  // another unit's, each doing the unit's whole prep again.
+  // two): 2048 rows a unit, 64 units 82 / 76, 128 units 83 / 78, 144 units 83 /
+  // 146; 128 rows a unit, 64 units 18.6 / 17.1, 128 units 19.2 / 18.0, 144
+  // units 19.2 / 29.0.
   if constexpr (!SPLIT) {
     const int64_t halves = (units + 7) / 8 * 16;
     if (halves <= device_cus()) {

@@ -31,7 +31,7 @@
 // to 10% faster still on grids of fewer tiles than CUs and slower on all
 // others, and is not kept.
 //
-// One hand-over (wait + barrier) per K-step, after MFMA kBarrierAt of the
+// One hand-over (wait + barrier) per K-step, after BARRIER MFMAs of the
 // first half step: by then every wave has read its second-half fragments, so
 // the step's slots are free, and the next step's rows have landed.  The
 // refills follow it, one DMA per few MFMAs (issued closer together they cost
