@@ -280,14 +280,17 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
   // t], are 8 (bf16) or 16 (fp32) bytes and the lane's JG columns of a group
   // neighbours; else they are read one by one.
   const int tap_mode = (a.w == 4 && (reinterpret_cast<uintptr_t>(a.conv_w) & 15) == 0) ? (a.conv_bf16 ? 1 : 2) : 0;
-  // fp8 scale (bf16 bits) of fragment block j's column
-  auto scale = [&](int j) {
-    uint32_t bits = 0x3f80u;   // 1
-    if constexpr (FP8) {
-      const int n = column(wn, j, lc);
-      bits = *col_scale_ptr(a, real_col<RECT, D>(a, n < a.N ? n : a.N - 1));
-    }
-    return bf16_bits_to_f32(bits);
+  // fp8: a q, k, v or z head's columns are one weight's, so one search, on the
+  // wave's scalars, finds the scales of the head at column nb.  (A search per
+  // fragment block and lane cost 4 us a tile: 2 layers of 14.8K rows, N = 7770,
+  // D = 256, 372 us so and 340 as it is.)
+  auto head_scales = [&](int nb) -> const uint16_t* {
+    if constexpr (FP8) return col_scale_ptr(a, real_col<RECT, D>(a, nb));
+    return nullptr;
+  };
+  auto scale = [&](const uint16_t* head, int c) {   // of the head's channel c
+    if constexpr (FP8) return bf16_bits_to_f32(head[c]);
+    return 1.f;
   };
   tile_drain();
   tile_pin(acc);
@@ -362,6 +365,8 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
       // ---- q, k or v head: conv, SiLU, (queries and keys) L2 norm
       const bool is_q = nb < a.C_q;
       const bool is_k = nb < a.C_k;   // q or k: normalised
+      const uint16_t* const head_sc = head_scales(nb);
+      const int rn = real_col<RECT, D>(a, nb);   // the head's first channel
       // destinations of the lane's JG columns of each group, row rbase
       const int hh = is_q ? nb / D : (is_k ? (nb - a.C_q) / D : (nb - a.C_k) / D);
       uint16_t* const head = static_cast<uint16_t*>(is_q ? a.Qbuf : (is_k ? a.Kbuf : a.Vbuf)) + ((int64_t)hh * T + t0) * D;
@@ -446,7 +451,7 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
           }
 #pragma unroll
           for (int jj = 0; jj < JG; ++jj) {
-            const float sc = scale(j0 + jj) * -kLog2e;
+            const float sc = scale(head_sc, ch0 - rn + jj) * -kLog2e;
 #pragma unroll
             for (int d = 0; d < 4; ++d) tp[jj][d] *= sc;
           }
@@ -515,7 +520,7 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
           const int ch0 = pad ? 0 : real_col<RECT, D>(a, nb + GW * gi + JG * lc);
           float sc[JG];
 #pragma unroll
-          for (int jj = 0; jj < JG; ++jj) sc[jj] = scale(j0 + jj);
+          for (int jj = 0; jj < JG; ++jj) sc[jj] = scale(head_sc, (pad ? 0 : ch0 - rn) + jj);
           static_for<U>([&](auto u_c) {
             constexpr int u = decltype(u_c)::value;
             if ((tail_rows >> u) & 1u) {
@@ -597,7 +602,7 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
         uint16_t* dst = static_cast<uint16_t*>(a.Zbuf) + ((int64_t)((nb - a.C_kv) / D) * T + t0) * D + GW * gi + JG * lc;
         float sc[JG];
 #pragma unroll
-        for (int jj = 0; jj < JG; ++jj) sc[jj] = scale(j0 + jj);
+        for (int jj = 0; jj < JG; ++jj) sc[jj] = scale(head_scales(nb), GW * gi + JG * lc + jj);
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
           f32x4 x[JG];
@@ -636,12 +641,16 @@ __global__ __launch_bounds__(kTileThreads<C>, 1) void proj_conv_kernel(ProjConvB
           // LDS operations of one wave complete in order: the reads below
           // see every lane's writes
           const int nc = a.N - nb_j < 16 ? a.N - nb_j : 16;
+          // lane c: the scale of column c (one load per block: a load per
+          // column waits for the stores of the one before; the shape above
+          // 340 us so, 301 as it is)
+          const float sc_lane = col_scale<TB>(a, real_col<RECT, D>(a, nb_j + (lc < nc ? lc : nc - 1)));
 #pragma clang loop unroll(disable)
           for (int c = 0; c < nc; ++c) {
             const int n = nb_j + c;
             const bool is_a = n < a.C_z + a.H_v;
             const int hv = is_a ? n - a.C_z : n - a.C_z - a.H_v;
-            const float sc = col_scale<TB>(a, real_col<RECT, D>(a, n));
+            const float sc = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sc_lane), c));
             const float x = tw[c * 16 * MI + ((((lane >> 2) ^ c) & (4 * MI - 1)) << 2) + (lane & 3)] * sc;
             const float v = is_a ? -__expf(a.a_log[hv]) * kLog2e * softplus(x + a.dt_bias[hv]) : fast_sigmoid(x);
             if (st_ok) ((is_a ? a.Gbuf : a.Bbuf) + (int64_t)hv * T)[row0 + r] = v;

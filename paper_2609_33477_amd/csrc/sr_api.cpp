@@ -23,6 +23,7 @@
 // then one state launch per group of <= 32 layers writes the states (the
 // pipelined bf16 scan, the fp32 scan, or the chunked kernel for the unfused
 // 96 x 192 heads).
+#include <atomic>
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -177,15 +178,15 @@ hipError_t sr::timed_launch(int kind, hipStream_t s, hipError_t (*launch)(void*)
 }
 
 int sr::device_cus() {
-  static int cache[64];
+  static std::atomic<int> cache[64];   // 0: not asked yet (threads may ask twice)
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-  if (cache[dev] == 0) {
-    int n = 0;
+  int n = cache[dev].load(std::memory_order_relaxed);
+  if (n == 0) {
     if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-    cache[dev] = n;
+    cache[dev].store(n, std::memory_order_relaxed);
   }
-  return cache[dev];
+  return n;
 }
 
 hipError_t sr::note_error(int kind, hipError_t e) { return note(kind, e); }
