@@ -2,14 +2,15 @@
 // and the conv tail (Appendix A: the conv state is the last w-1 inputs of the
 // q, k, v channels).
 //
-// conv_gate_kernel: one wave per (row block, head); each lane owns d/64 (or one)
-// channels of the head and walks the block's rows, keeping the previous w-1
-// raw projection values in registers, so every projection element is read
-// from HBM once (plus a (w-1)-row halo per block).  History is masked at
-// segment starts: replay has no inputs before its first row.  Key heads are
-// L2-normalised with a wave reduction.  The last y-block of the grid computes
-// the per-(row, value head) gates:
+// conv_gate_kernel (fp32 operands, square heads): a block per (block of rows,
+// head), its rows in parallel; history is masked at segment starts (replay has
+// no inputs before its first row) and key heads are L2-normalised with a wave
+// reduction.  One more block per row block computes the per-(row, value head)
+// gates:
 //   g = log alpha = -exp(A_log) * softplus(a + dt_bias),  beta = sigmoid(b).
+// conv_gate_rect_kernel (bf16 operands, d_k = 96 and d_v = 192 with an odd
+// number of value heads): a wave per (row block, head) walks the rows.  Every
+// other bf16 shape runs this step inside the fused projection.
 // Outputs are head-major ([H][T][d], [H][T]) so the scan reads each 64-row
 // chunk of a head as one contiguous block.
 //
@@ -17,13 +18,12 @@
 // the segment's last w-1 rows as dot products (W_q is used nowhere else), and
 // zeros at positions before the segment's first row (every channel); the k | v
 // channels of existing rows are written with k and v.  These blocks need
-// nothing the conv computes and ride behind it in one grid (a launch of their
-// own when there are no rows).  With bf16 anchors the tail is computed inside
-// the fused projection's grid.
+// nothing the conv computes and ride behind it in one grid (tail_rides_conv; a
+// launch of their own where there are no rows or too many of these blocks for
+// that grid).  With bf16 anchors the tail is computed inside the fused
+// projection's grid.
 #include "sr_device.hpp"
 #include "tail_q.hpp"
-
-#include <type_traits>
 
 namespace sr {
 namespace {
@@ -49,11 +49,8 @@ __device__ __forceinline__ float sigmoid(float x) { return 1.f / (1.f + expf(-x)
 constexpr int kTailThreads = 256;
 constexpr int kTailChannels = 4;   // one channel per wave: the channels' loads run in parallel
 
-// 8 consecutive elements starting at element i, as fp32.
-template <typename T>
-__device__ __forceinline__ void load8(const void* p, int64_t i, float* out);
-template <>
-__device__ __forceinline__ void load8<float>(const void* p, int64_t i, float* out) {
+// 8 consecutive fp32 elements starting at element i
+__device__ __forceinline__ void load8(const void* p, int64_t i, float* out) {
   const float4* q = reinterpret_cast<const float4*>(static_cast<const float*>(p) + i);
   const float4 x = q[0], y = q[1];
   out[0] = x.x; out[1] = x.y; out[2] = x.z; out[3] = x.w;
@@ -64,7 +61,7 @@ __device__ __forceinline__ void load8<float>(const void* p, int64_t i, float* ou
 __host__ __device__ inline int tail_blocks_y(const TailArgs& a) { return (a.c_tail + kTailChannels - 1) / kTailChannels; }
 
 // Block (segment b, channels 4 yb .. + 3); every thread of a kTailThreads block
-template <typename TA, typename TW, typename TT>
+template <typename TT>
 __device__ __forceinline__ void tail_block(const TailArgs& a, int b, int yb) {
   constexpr int WMAX = 4;
   const int slot = a.slot_ids ? a.slot_ids[b] : b;
@@ -90,13 +87,13 @@ __device__ __forceinline__ void tail_block(const TailArgs& a, int b, int yb) {
     float acc[WMAX - 1] = {0.f, 0.f, 0.f};
     for (int k = lane * 8; k < a.D; k += 64 * 8) {
       float wv[8];
-      load8<TW>(a.w_q, (int64_t)c * a.D + k, wv);
+      load8(a.w_q, (int64_t)c * a.D + k, wv);
 #pragma unroll
       for (int pos = 0; pos < WMAX - 1; ++pos) {
         const int64_t t = s1 - w1 + pos;
         if (pos < w1 && t >= s0) {
           float xv[8];
-          load8<TA>(a.anchors, t * a.D + k, xv);
+          load8(a.anchors, t * a.D + k, xv);
 #pragma unroll
           for (int j = 0; j < 8; ++j) acc[pos] = fmaf(xv[j], wv[j], acc[pos]);
         }
@@ -107,10 +104,8 @@ __device__ __forceinline__ void tail_block(const TailArgs& a, int b, int yb) {
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) acc[pos] += __shfl_xor(acc[pos], off);
     if (lane == 0) {
-      const float scale = std::is_same<TW, fp8_t>::value ? Elem<bf16_t>::load(a.s_q, c) : 1.f;
       for (int pos = 0; pos < w1; ++pos)
-        if (s1 - w1 + pos >= s0)
-          Elem<TT>::store(a.tail, ((int64_t)slot * a.c_tail + c) * w1 + pos, acc[pos] * scale);
+        if (s1 - w1 + pos >= s0) Elem<TT>::store(a.tail, ((int64_t)slot * a.c_tail + c) * w1 + pos, acc[pos]);
     }
   }
 }
@@ -121,7 +116,7 @@ __device__ __forceinline__ void tail_block(const TailArgs& a, int b, int yb) {
 // channels of one row), each lane reading the w raw rows its conv needs, so no
 // row waits for the one before it; a key's sum of squares is reduced over the
 // LPH lanes of its row.
-template <typename OUT, typename CW, typename TT, int DH, int ROWS>
+template <typename CW, typename TT, int DH, int ROWS>
 __global__ __launch_bounds__(kConvThreads) void conv_gate_kernel(ConvGateArgs a, TailArgs tail) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
   constexpr int CPL = DH >= 64 ? DH / 64 : 1;   // channels per lane
@@ -138,11 +133,9 @@ __global__ __launch_bounds__(kConvThreads) void conv_gate_kernel(ConvGateArgs a,
 
   if ((int)blockIdx.y > n_heads) {
     static_assert(kConvThreads == kTailThreads, "tail blocks");
-    if constexpr (std::is_same<OUT, float>::value) {
-      const int64_t i = (int64_t)(blockIdx.y - n_heads - 1) * gridDim.x + blockIdx.x;
-      const int ty = tail_blocks_y(tail);
-      if (i < (int64_t)tail.n_seg * ty) tail_block<float, float, TT>(tail, (int)(i / ty), (int)(i % ty));
-    }
+    const int64_t i = (int64_t)(blockIdx.y - n_heads - 1) * gridDim.x + blockIdx.x;
+    const int ty = tail_blocks_y(tail);
+    if (i < (int64_t)tail.n_seg * ty) tail_block<TT>(tail, (int)(i / ty), (int)(i % ty));
     return;
   }
   if ((int)blockIdx.y == n_heads) {
@@ -211,7 +204,7 @@ __global__ __launch_bounds__(kConvThreads) void conv_gate_kernel(ConvGateArgs a,
     if (live) {
       const int64_t base = ((int64_t)hh * a.T + t) * DH + sub * CPL;
 #pragma unroll
-      for (int q = 0; q < CPL; ++q) Elem<OUT>::store(dst, base + q, act[q]);
+      for (int q = 0; q < CPL; ++q) Elem<float>::store(dst, base + q, act[q]);
       if (a.tail && slot >= 0 && t >= s1 - (w - 1)) {
         const int pos = (int)(t - (s1 - (w - 1)));
 #pragma unroll
@@ -225,7 +218,7 @@ __global__ __launch_bounds__(kConvThreads) void conv_gate_kernel(ConvGateArgs a,
 // 64 rows per block once those blocks fill the card, else 16: a block's passes
 // over its rows are a chain of memory round trips (256 rows, two heads of 32:
 // 20 blocks of 8 passes 10.3 us, 80 of 2 passes with the tail's blocks 8 us).
-template <typename OUT, typename CW, typename TT, int DH>
+template <typename CW, typename TT, int DH>
 hipError_t run_conv(const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) {
   if (a.T == 0) return hipSuccess;
   const int n_heads = a.H_k + a.H_v;
@@ -236,8 +229,8 @@ hipError_t run_conv(const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) 
     return hipGetLastError();
   };
   if ((a.T + kRowsPerBlock - 1) / kRowsPerBlock * (n_heads + 1) >= 4 * device_cus())
-    return launch(conv_gate_kernel<OUT, CW, TT, DH, kRowsPerBlock>, kRowsPerBlock);
-  return launch(conv_gate_kernel<OUT, CW, TT, DH, 16>, 16);
+    return launch(conv_gate_kernel<CW, TT, DH, kRowsPerBlock>, kRowsPerBlock);
+  return launch(conv_gate_kernel<CW, TT, DH, 16>, 16);
 }
 
 // Heads whose key and value widths differ (Appendix A: OLMo-Hybrid's
@@ -245,7 +238,7 @@ hipError_t run_conv(const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) 
 // channels l, l + 64, ... of its head, walking the block's rows as above; a
 // key head's sum of squares is reduced over the wave.  G is written as
 // log2 alpha, the convention of the chunk kernel that reads it.
-template <typename OUT, typename CW, typename TT, int DK, int DV>
+template <typename CW, typename TT, int DK, int DV>
 __global__ __launch_bounds__(kConvThreads) void conv_gate_rect_kernel(ConvGateArgs a) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
   constexpr int QMAX = ((DK > DV ? DK : DV) + 63) / 64;   // channels per lane, at most
@@ -336,7 +329,7 @@ __global__ __launch_bounds__(kConvThreads) void conv_gate_rect_kernel(ConvGateAr
     for (int q = 0; q < QMAX; ++q) {
       const int ch = lane + 64 * q;
       if (ch < DH) {
-        Elem<OUT>::store(dst, base + ch, act[q]);
+        Elem<bf16_t>::store(dst, base + ch, act[q]);
         if (tail_row) Elem<TT>::store(a.tail, ((int64_t)slot * a.c_tail + a.tail_kv_off + c0 + ch) * (w - 1) + pos, raw[q]);
       }
     }
@@ -349,57 +342,51 @@ __global__ __launch_bounds__(kConvThreads) void conv_gate_rect_kernel(ConvGateAr
   }
 }
 
-template <typename OUT, typename CW, typename TT, int DK, int DV>
+template <typename CW, typename TT, int DK, int DV>
 hipError_t run_conv_rect(const ConvGateArgs& a, hipStream_t s) {
   if (a.T == 0) return hipSuccess;
   const int n_heads = a.H_k + a.H_v;
   constexpr int HPB = kConvThreads / 64;   // heads per block
   dim3 grid((unsigned)((a.T + kRowsPerBlock - 1) / kRowsPerBlock), (n_heads + HPB - 1) / HPB + 1);
-  hipLaunchKernelGGL((conv_gate_rect_kernel<OUT, CW, TT, DK, DV>), grid, dim3(kConvThreads), 0, s, a);
+  hipLaunchKernelGGL((conv_gate_rect_kernel<CW, TT, DK, DV>), grid, dim3(kConvThreads), 0, s, a);
   return hipGetLastError();
 }
 
-template <typename OUT, typename CW, typename TT>
-hipError_t conv_by_head(int d, const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) {
-  if (a.d_k != a.d_v) {
-    if constexpr (std::is_same<OUT, bf16_t>::value) {
-      if (a.d_k == 96 && a.d_v == 192) return run_conv_rect<OUT, CW, TT, 96, 192>(a, s);
-    }
-    return hipErrorInvalidValue;
-  }
+// fp32 operands: square heads.  bf16 operands: the rectangular heads that the
+// fused projection does not take (it takes every square bf16 head).
+template <typename CW, typename TT>
+hipError_t conv_by_head(int op_dtype, int d, const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) {
+  if (op_dtype == SR_BF16)
+    return a.d_k == 96 && a.d_v == 192 && tail.n_seg == 0 ? run_conv_rect<CW, TT, 96, 192>(a, s) : hipErrorInvalidValue;
+  if (op_dtype != SR_F32 || a.d_k != a.d_v) return hipErrorInvalidValue;
   switch (d) {
-    case 32: return run_conv<OUT, CW, TT, 32>(a, tail, s);
-    case 64: return run_conv<OUT, CW, TT, 64>(a, tail, s);
-    case 128: return run_conv<OUT, CW, TT, 128>(a, tail, s);
+    case 32: return run_conv<CW, TT, 32>(a, tail, s);
+    case 64: return run_conv<CW, TT, 64>(a, tail, s);
+    case 128: return run_conv<CW, TT, 128>(a, tail, s);
   }
   return hipErrorInvalidValue;
 }
 
-template <typename OUT, typename CW>
-hipError_t conv_by_tail(int tail_dtype, int d, const ConvGateArgs& a, const TailArgs& tail, hipStream_t s) {
-  if (tail_dtype == SR_F32) return conv_by_head<OUT, CW, float>(d, a, tail, s);
-  if (tail_dtype == SR_BF16) return conv_by_head<OUT, CW, bf16_t>(d, a, tail, s);
+template <typename CW>
+hipError_t conv_by_tail(int op_dtype, int tail_dtype, int d, const ConvGateArgs& a, const TailArgs& tail,
+                        hipStream_t s) {
+  if (tail_dtype == SR_F32) return conv_by_head<CW, float>(op_dtype, d, a, tail, s);
+  if (tail_dtype == SR_BF16) return conv_by_head<CW, bf16_t>(op_dtype, d, a, tail, s);
   return hipErrorInvalidValue;
-}
-
-template <typename TA, typename TW, typename TT>
-__global__ __launch_bounds__(kTailThreads) void tail_kernel(TailArgs a) {
-  if (a.err && *a.err) return;   // the call's table check failed: write nothing
-  tail_block<TA, TW, TT>(a, blockIdx.x, blockIdx.y);
-}
-
-template <typename TA, typename TW, typename TT>
-hipError_t run_tail(const TailArgs& a, hipStream_t s) {
-  if (a.n_seg == 0 || a.w < 2 || a.c_tail == 0) return hipSuccess;
-  dim3 grid(a.n_seg, tail_blocks_y(a));
-  hipLaunchKernelGGL((tail_kernel<TA, TW, TT>), grid, dim3(kTailThreads), 0, s, a);
-  return hipGetLastError();
 }
 
 template <typename TT>
-hipError_t tail_by_input(int ad, int wd, const TailArgs& a, hipStream_t s) {
-  if (ad == SR_F32 && wd == SR_F32) return run_tail<float, float, TT>(a, s);
-  return hipErrorInvalidValue;
+__global__ __launch_bounds__(kTailThreads) void tail_kernel(TailArgs a) {
+  if (a.err && *a.err) return;   // the call's table check failed: write nothing
+  tail_block<TT>(a, blockIdx.x, blockIdx.y);
+}
+
+template <typename TT>
+hipError_t run_tail(const TailArgs& a, hipStream_t s) {
+  if (a.n_seg == 0 || a.w < 2 || a.c_tail == 0) return hipSuccess;
+  dim3 grid(a.n_seg, tail_blocks_y(a));
+  hipLaunchKernelGGL((tail_kernel<TT>), grid, dim3(kTailThreads), 0, s, a);
+  return hipGetLastError();
 }
 
 // The q-tail blocks of tail_q.hpp in a grid of their own (bf16 anchors on a
@@ -418,13 +405,8 @@ hipError_t launch_conv_gate(int op_dtype, int conv_dtype, int tail_dtype, int d_
                             const ConvGateArgs& a, const TailArgs* tail, hipStream_t s) {
   TailArgs t{};                              // n_seg = 0: no tail blocks
   if (tail && tail->w >= 2) t = *tail;
-  if (op_dtype == SR_F32) {
-    if (conv_dtype == SR_F32) return conv_by_tail<float, float>(tail_dtype, d_head, a, t, s);
-    if (conv_dtype == SR_BF16) return conv_by_tail<float, bf16_t>(tail_dtype, d_head, a, t, s);
-  } else if (op_dtype == SR_BF16 && t.n_seg == 0) {
-    if (conv_dtype == SR_F32) return conv_by_tail<bf16_t, float>(tail_dtype, d_head, a, t, s);
-    if (conv_dtype == SR_BF16) return conv_by_tail<bf16_t, bf16_t>(tail_dtype, d_head, a, t, s);
-  }
+  if (conv_dtype == SR_F32) return conv_by_tail<float>(op_dtype, tail_dtype, d_head, a, t, s);
+  if (conv_dtype == SR_BF16) return conv_by_tail<bf16_t>(op_dtype, tail_dtype, d_head, a, t, s);
   return hipErrorInvalidValue;
 }
 
@@ -438,8 +420,9 @@ hipError_t launch_tail(int anchor_dtype, int weight_dtype, int tail_dtype, const
     else return hipErrorInvalidValue;
     return hipGetLastError();
   }
-  if (tail_dtype == SR_F32) return tail_by_input<float>(anchor_dtype, weight_dtype, a, s);
-  if (tail_dtype == SR_BF16) return tail_by_input<bf16_t>(anchor_dtype, weight_dtype, a, s);
+  if (anchor_dtype != SR_F32 || weight_dtype != SR_F32) return hipErrorInvalidValue;
+  if (tail_dtype == SR_F32) return run_tail<float>(a, s);
+  if (tail_dtype == SR_BF16) return run_tail<bf16_t>(a, s);
   return hipErrorInvalidValue;
 }
 
