@@ -21,11 +21,12 @@
 // the state; its state wave w (w < d/32) then advances state columns
 // [32w, 32w+32), d/32 MFMA accumulator tiles.  At d < 128 the other waves take
 // the Gram tiles and W = Tw K, so the state waves' chain of products is shorter.
-// What bounds a unit is this chain of short dependent steps, ten barriers a
+// What bounds a unit is this chain of short dependent steps, eleven barriers a
 // chunk; two teams (d <= 64, whose LDS holds both) run it for two chunks at
-// once and hand the state from one to the other through the LDS.  One unit of
-// 256 rows at d = 32: 45 us with one team and full products, see launch_scan
-// for when which is taken.
+// once, twelve barriers a pair, and hand the state from one to the other through
+// the LDS.  One unit of 256 rows at d = 32: 45 us with one team and full
+// products, 35 us with two teams and triangular ones; run_scan says when which
+// is taken.
 // Operand precision: everything is fp32, K and V as they arrive; beta and the decay
 // factors are folded into T (rounded once) and into Delta (rounded once), so no
 // value is rounded twice.  The state is fp32 throughout.  The two products
@@ -40,7 +41,6 @@
 #include "sr_device.hpp"
 
 #include <cstddef>
-#include <type_traits>
 
 namespace sr {
 namespace {
@@ -49,15 +49,16 @@ constexpr int kC = 64;       // chunk rows
 constexpr int kFP = 68;      // fp32 pitch of A and T
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <typename OP, int D>
+using MF = Mfma<float>;
+
+template <int D>
 struct ScanCfg {
   static constexpr int NSW = D / 32;                   // state waves: wave w owns columns [32w, 32w+32)
   static constexpr int NW = NSW < 4 ? 4 : NSW;          // waves: the rest share the chunk products
   static constexpr int THREADS = 64 * NW;
-  static constexpr int EB = std::is_same<OP, float>::value ? 4 : 2;
-  static constexpr int PADE = 16 / EB;
-  static constexpr int KP = D + PADE;      // pitch of Kr and W (elements)
-  static constexpr int CP = kC + PADE;     // pitch of Kt, Vt, Tu, Tw
+  static constexpr int EB = 4;             // bytes of an element
+  static constexpr int KP = D + 4;         // pitch of Kr and W (elements)
+  static constexpr int CP = kFP;           // pitch of Kt, Vt, Tu, Tw: Tw takes T's place, Tu A's
   static constexpr int R1_KR = kC * KP * EB;
   static constexpr int R1_A = kC * kFP * 4;
   static constexpr int R1 = R1_KR > R1_A ? R1_KR : R1_A;   // K rows, then A, Tu, W
@@ -73,55 +74,27 @@ struct ScanCfg {
   static constexpr int VPP = 16 / EB;                   // elements per piece
   static constexpr int PPR = D / VPP;                   // pieces per row
   static_assert(PIECES % THREADS == 0, "chunk split");
-  static_assert(std::is_same<OP, float>::value && CP == kFP && kC * CP * EB <= R1, "Tw takes T's place, Tu A's");
 };
 
 // Standard-order operand fragment from a row-major LDS matrix.
-template <typename OP>
-__device__ __forceinline__ typename Mfma<OP>::frag frag_std(const char* base, int pitch, int row, int k);
-template <>
-__device__ __forceinline__ float frag_std<float>(const char* base, int pitch, int row, int k) {
+__device__ __forceinline__ float frag_std(const char* base, int pitch, int row, int k) {
   return *reinterpret_cast<const float*>(base + ((size_t)row * pitch + k) * 4);
 }
 
 // Operand fragment whose k slots follow the accumulator row layout of a
 // 32-row tile starting at column `col0`: step s, lane half h.
-template <typename OP>
-__device__ __forceinline__ typename Mfma<OP>::frag frag_perm(const char* base, int pitch, int row, int col0,
-                                                              int s, int h, bool negate);
-template <>
-__device__ __forceinline__ float frag_perm<float>(const char* base, int pitch, int row, int col0, int s, int h,
-                                                  bool negate) {
+__device__ __forceinline__ float frag_perm(const char* base, int pitch, int row, int col0, int s, int h, bool negate) {
   const float v = *reinterpret_cast<const float*>(base + ((size_t)row * pitch + col0 + 8 * (s >> 2) + 4 * h + (s & 3)) * 4);
   return negate ? -v : v;
 }
 
-// Accumulator registers of one 32x32 tile as the B operand of MFMA step s.
-template <typename OP>
-__device__ __forceinline__ typename Mfma<OP>::frag frag_acc(const f32x16& acc, int s);
-template <>
-__device__ __forceinline__ float frag_acc<float>(const f32x16& acc, int s) { return acc[s]; }
-
-template <typename OP>
-__device__ __forceinline__ void store_op(char* base, int idx, float v);
-template <>
-__device__ __forceinline__ void store_op<float>(char* base, int idx, float v) {
-  reinterpret_cast<float*>(base)[idx] = v;
-}
-
-// Four consecutive operand values (8- or 16-byte aligned destination).
-template <typename OP>
-__device__ __forceinline__ void store4_op(char* base, int idx, const float* v);
-template <>
-__device__ __forceinline__ void store4_op<float>(char* base, int idx, const float* v) {
+// Four consecutive values (16-byte aligned destination).
+__device__ __forceinline__ void store4(char* base, int idx, const float* v) {
   *reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + idx) = make_float4(v[0], v[1], v[2], v[3]);
 }
 
-// Scatter a 16-byte piece (VPP elements of one row) into a transposed matrix.
-template <typename OP>
-__device__ __forceinline__ void store_transposed(char* base, int pitch, int col, int row, const uint4& v);
-template <>
-__device__ __forceinline__ void store_transposed<float>(char* base, int pitch, int col, int row, const uint4& v) {
+// Scatter a 16-byte piece (4 elements of one row) into a transposed matrix.
+__device__ __forceinline__ void store_transposed(char* base, int pitch, int col, int row, const uint4& v) {
   float* p = reinterpret_cast<float*>(base);
   p[(col + 0) * pitch + row] = __uint_as_float(v.x);
   p[(col + 1) * pitch + row] = __uint_as_float(v.y);
@@ -129,11 +102,10 @@ __device__ __forceinline__ void store_transposed<float>(char* base, int pitch, i
   p[(col + 3) * pitch + row] = __uint_as_float(v.w);
 }
 
-template <typename OP, int D, int TEAMS>
+template <int D, int TEAMS>
 __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_scan_kernel(ScanArgs a) {
   if (a.err && *a.err) return;   // the call's table check failed: write nothing
-  using CF = ScanCfg<OP, D>;
-  using MF = Mfma<OP>;
+  using CF = ScanCfg<D>;
   constexpr int NW = CF::NW, NSW = CF::NSW, EB = CF::EB, KP = CF::KP, CP = CF::CP;
   constexpr int NT = D / 32;  // 32-row tiles along d
   constexpr int STEP = TEAMS * kC;     // rows the teams take per round
@@ -241,8 +213,8 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
       const int p = tid + i * CF::THREADS;
       const int row = p / CF::PPR, cc = p % CF::PPR;
       *reinterpret_cast<uint4*>(R1 + (row * KP + cc * CF::VPP) * EB) = pk[i];
-      store_transposed<OP>(Kt, CP, cc * CF::VPP, row, pk[i]);
-      store_transposed<OP>(Vt, CP, cc * CF::VPP, row, pv[i]);
+      store_transposed(Kt, CP, cc * CF::VPP, row, pk[i]);
+      store_transposed(Vt, CP, cc * CF::VPP, row, pv[i]);
     }
     if (tid < kC) {
       gs[tid] = pg * kLog2e;   // log2 alpha: every decay factor below is an exp2
@@ -275,8 +247,8 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
       const int ti = (q + 1) >> 1, tj = q >> 1;
 #pragma unroll
       for (int s = 0; s < D / MF::K; ++s) {
-        const auto fa = frag_std<OP>(R1, KP, 32 * ti + fr, s * MF::K + fk);
-        const auto fb = frag_std<OP>(R1, KP, 32 * tj + fr, s * MF::K + fk);
+        const auto fa = frag_std(R1, KP, 32 * ti + fr, s * MF::K + fk);
+        const auto fb = frag_std(R1, KP, 32 * tj + fr, s * MF::K + fk);
         MF::mma(gam[n], fa, fb);
       }
     }
@@ -351,8 +323,8 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
       const float4 g4 = *reinterpret_cast<const float4*>(eG + j);
       const float u[4] = {t.x * b4.x, t.y * b4.y, t.z * b4.z, t.w * b4.w};
       const float v[4] = {u[0] * g4.x, u[1] * g4.y, u[2] * g4.z, u[3] * g4.w};
-      store4_op<OP>(Tu, i * CP + j, u);
-      store4_op<OP>(Tw, i * CP + j, v);
+      store4(Tu, i * CP + j, u);
+      store4(Tw, i * CP + j, v);
     }
     lds_barrier();
 
@@ -369,8 +341,8 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
         Uacc[ti] = zero16();
 #pragma unroll
         for (int s = 0; s < 32 * (ti + 1) / MF::K; ++s) {
-          const auto fa = frag_std<OP>(Tu, CP, 32 * ti + fr, s * MF::K + fk);
-          const auto fb = frag_std<OP>(Vt, CP, 32 * wid + fr, s * MF::K + fk);
+          const auto fa = frag_std(Tu, CP, 32 * ti + fr, s * MF::K + fk);
+          const auto fb = frag_std(Vt, CP, 32 * wid + fr, s * MF::K + fk);
           MF::mma(Uacc[ti], fa, fb);
         }
         __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
@@ -385,8 +357,8 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
       auto w_steps = [&](int lo) {
 #pragma unroll
         for (int s = 0; s < 32 / MF::K; ++s) {
-          const auto fa = frag_std<OP>(Tw, CP, 32 * ti + fr, lo + s * MF::K + fk);
-          const auto fb = frag_std<OP>(Kt, CP, 32 * td + fr, lo + s * MF::K + fk);
+          const auto fa = frag_std(Tw, CP, 32 * ti + fr, lo + s * MF::K + fk);
+          const auto fb = frag_std(Kt, CP, 32 * td + fr, lo + s * MF::K + fk);
           MF::mma(Wacc[n], fa, fb);
         }
         __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
@@ -403,13 +375,13 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
       if ((WW0 > 0 && wid < WW0) || q >= 2 * NT) continue;
       const int ti = q / NT, td = q % NT;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) store_op<OP>(Wr, (32 * ti + acc_row(r, lane_r)) * KP + 32 * td + fr, Wacc[n][r]);
+      for (int r = 0; r < 16; ++r) reinterpret_cast<float*>(Wr)[(32 * ti + acc_row(r, lane_r)) * KP + 32 * td + fr] = Wacc[n][r];
     }
     lds_barrier();
 
     // ---- 9. Delta = U - W M0 (state from registers), Delta' = e^{G_C - G} Delta
     auto advance = [&]() {
-      typename MF::frag dfrag[2][32 / MF::K];
+      float dfrag[2][32 / MF::K];
 #pragma unroll
       for (int ti = 0; ti < 2; ++ti) {
         f32x16 acc = Uacc[ti];
@@ -417,8 +389,8 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
         for (int td = 0; td < NT; ++td) {
 #pragma unroll
           for (int s = 0; s < 32 / MF::K; ++s) {
-            const auto fa = frag_perm<OP>(Wr, KP, 32 * ti + fr, 32 * td, s, h2, true);
-            const auto fb = frag_acc<OP>(M[td], s);
+            const auto fa = frag_perm(Wr, KP, 32 * ti + fr, 32 * td, s, h2, true);
+            const float fb = M[td][s];
             MF::mma(acc, fa, fb);
           }
           __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
@@ -426,7 +398,7 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] *= eD[32 * ti + acc_row(r, lane_r)];
 #pragma unroll
-        for (int s = 0; s < 32 / MF::K; ++s) dfrag[ti][s] = frag_acc<OP>(acc, s);
+        for (int s = 0; s < 32 / MF::K; ++s) dfrag[ti][s] = acc[s];
       }
 
       // ---- 10. M = e^{G_C} M0 + K^T Delta'
@@ -439,7 +411,7 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
         for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
           for (int s = 0; s < 32 / MF::K; ++s) {
-            const auto fa = frag_perm<OP>(Kt, CP, 32 * td + fr, 32 * ti, s, h2, false);
+            const auto fa = frag_perm(Kt, CP, 32 * td + fr, 32 * ti, s, h2, false);
             MF::mma(M[td], fa, dfrag[ti][s]);
           }
         __builtin_amdgcn_sched_barrier(0);   // bounds the loads hoisted ahead of the products
@@ -489,18 +461,18 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
 // team / two): d = 32, 256 units 161 / 131, 272 units 201 / 256, 1024 units
 // 412 / 530; d = 64, 256 units 247 / 209, 272 units 486 / 407, 1024 units
 // 994 / 848.
-template <typename OP, int D>
+template <int D>
 hipError_t run_scan(const ScanArgs& a, hipStream_t s) {
   const int64_t units = (int64_t)a.n_seg * a.n_layers * a.H_v;
   if (units == 0) return hipSuccess;
-  constexpr int THREADS = ScanCfg<OP, D>::THREADS;
+  constexpr int THREADS = ScanCfg<D>::THREADS;
   if constexpr (D <= 64) {
     if (D == 64 || units <= device_cus()) {
-      hipLaunchKernelGGL((gdn_scan_kernel<OP, D, 2>), dim3((unsigned)units), dim3(2 * THREADS), 0, s, a);
+      hipLaunchKernelGGL((gdn_scan_kernel<D, 2>), dim3((unsigned)units), dim3(2 * THREADS), 0, s, a);
       return hipGetLastError();
     }
   }
-  if constexpr (D != 64) hipLaunchKernelGGL((gdn_scan_kernel<OP, D, 1>), dim3((unsigned)units), dim3(THREADS), 0, s, a);
+  if constexpr (D != 64) hipLaunchKernelGGL((gdn_scan_kernel<D, 1>), dim3((unsigned)units), dim3(THREADS), 0, s, a);
   return hipGetLastError();
 }
 
@@ -510,9 +482,9 @@ hipError_t launch_scan(int op_dtype, int d_head, const ScanArgs& a, hipStream_t 
   if (op_dtype == SR_BF16) return launch_scan_bf16(d_head, a, s);
   if (op_dtype == SR_F32) {
     switch (d_head) {
-      case 32: return run_scan<float, 32>(a, s);
-      case 64: return run_scan<float, 64>(a, s);
-      case 128: return run_scan<float, 128>(a, s);
+      case 32: return run_scan<32>(a, s);
+      case 64: return run_scan<64>(a, s);
+      case 128: return run_scan<128>(a, s);
     }
   }
   return hipErrorInvalidValue;
