@@ -133,17 +133,19 @@ def algorithmic_work(wl, with_q=True):
     # the fused projection covers PROJ_LAYERS_PER_LAUNCH layers per launch:
     # its per-launch work is the average over the call's launches
     proj_layers = n_layers / -(-n_layers // PROJ_LAYERS_PER_LAUNCH)
+    tail = c_q * D * wb + tail_rows * ((c_q + c_kv) * tb + D * es)
     return {
         # one launch per layer
         "proj_gemm": ("mfma", 2.0 * T * D * N),
-        "conv_gate": ("hbm", T * N * 4 + T * c_kv * es + 2 * T * hv * 4),
+        # (fp32 anchors: with the q part of the tail behind it)
+        "conv_gate": ("hbm", T * N * 4 + T * c_kv * es + 2 * T * hv * 4 + (tail if sh.anchor_dtype == "f32" else 0)),
         # fused projection + conv epilogue: the contraction is the bound; its
         # HBM traffic is anchors + weights in, k_hat | v | G | beta out.  The
         # q part of the conv tail (a GEMM over the live segments' last w-1
         # rows) runs in the same grid.
         "proj_conv": ("mfma", proj_layers * (2.0 * T * D * N + 2.0 * tail_rows * D * c_q)),
-        # fp32 anchors: the tail's own launch
-        "tail": ("hbm", c_q * D * wb + tail_rows * ((c_q + c_kv) * tb + D * es)),
+        # the tail's own launch (96 x 192 heads, an odd number of value heads)
+        "tail": ("hbm", tail),
         # one launch per call: the varlen tables in, one flag word out, and on
         # the fused path the rows' segment info (16 bytes per row) out
         "validate": ("hbm", (2 * len(wl.seg_lens) + 1) * 4 + 4

@@ -244,9 +244,15 @@ sr_status sr_replay_state_noalloc(const sr_shape* shape, int32_t n_layers, const
 /* Kernels the library launches, as indexed by sr_kernel_timing_read(). */
 typedef enum sr_kernel_kind {
   SR_KERNEL_PROJ_GEMM = 0,   /* anchor projection (MFMA), fp32 path           */
-  SR_KERNEL_CONV_GATE = 1,   /* conv + SiLU + key norm + gates + k|v tail,
-                                fp32 path                                     */
-  SR_KERNEL_TAIL = 2,        /* q part of the conv tail + zero fill           */
+  SR_KERNEL_CONV_GATE = 1,   /* conv + SiLU + key norm + gates + k|v tail:
+                                fp32 path and 96 x 192 heads with an odd
+                                number of value heads; on the fp32 path with
+                                the rest of the tail in the same launch       */
+  SR_KERNEL_TAIL = 2,        /* q part of the conv tail + zero fill, where it
+                                is a launch of its own: fp32 path without rows
+                                or with more (segment, channel) blocks than
+                                the conv's grid takes, and the 96 x 192 heads
+                                above                                         */
   SR_KERNEL_GDN_SCAN = 3,    /* chunked state accumulation                    */
   SR_KERNEL_PROJ_CONV = 4,   /* projection fused with conv, SiLU, key norm,
                                 gates and the k|v tail (bf16 / fp8 path); one

@@ -19,7 +19,9 @@
 //     proj_gemm    anchors x [W_k; W_v; W_a; W_b]^T -> P (fp32 workspace)
 //     conv_gate    P -> k_hat, v, log alpha, beta, k | v tail; on the fp32 path
 //                  blocks behind it write the tail's q part and leading zeros
-//     tail         the same as a launch of its own (96 x 192 heads; no rows)
+//     tail         the same as a launch of its own (96 x 192 heads; fp32 path
+//                  without rows or with more of these blocks than the conv's
+//                  grid takes)
 // then one state launch per group of <= 32 layers writes the states (the
 // pipelined bf16 scan, the fp32 scan, or the chunked kernel for the unfused
 // 96 x 192 heads).

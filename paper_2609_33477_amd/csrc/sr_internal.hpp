@@ -156,9 +156,9 @@ hipError_t launch_conv_gate(int op_dtype, int conv_dtype, int tail_dtype, int d_
 inline bool tail_rides_conv(const TailArgs& a, int64_t T) {
   return T > 0 && (int64_t)a.n_seg * ((a.c_tail + 3) / 4) <= 60000 * ((T + 63) / 64);
 }
-// fp32 anchors: per-segment dot products (without rows; with them the conv's
-// grid carries these blocks); bf16 anchors: the q-tail blocks on their own
-// (the fused projection's grid carries them when it runs)
+// fp32 anchors: per-segment dot products, where tail_rides_conv does not hold
+// (else the conv's grid carries these blocks); bf16 anchors: the q-tail blocks
+// on their own (the fused projection's grid carries them when it runs)
 hipError_t launch_tail(int anchor_dtype, int weight_dtype, int tail_dtype, const TailArgs& a,
                        hipStream_t s);
 

@@ -147,6 +147,22 @@ def test_f32_scan_and_conv_edges(heads, layers, lens, d):
     check_pairs(dev, [(li, b) for li in range(layers) for b in range(len(lens))], TOL_F32)
 
 
+def test_f32_tail_too_large_to_ride_behind_the_conv():
+    """Hundreds of segments with next to no rows: more (segment, 4 channels)
+    tail blocks than fit behind the conv's one row block, so the tail keeps a
+    launch of its own; empty segments get zero states and tails."""
+    lens = [0] * 200
+    lens[3], lens[77], lens[199] = 1, 40, 2
+    heads, d = 16, 32
+    assert len(lens) * (3 * heads * d // 4) > 60000      # tail_rides_conv's bound for up to 64 rows
+    wl = W.make_workload("f32_tail", _f32_shape(64, heads, d), lens, seed=9)
+    dev = upload(wl)
+    run(dev)
+    check_pairs(dev, [(0, 3), (0, 77), (0, 199)], TOL_F32)
+    empty = [b for b, n in enumerate(lens) if n == 0]
+    assert torch.all(dev.layers[0].state_out[empty] == 0) and torch.all(dev.layers[0].tail_out[empty] == 0)
+
+
 @pytest.mark.parametrize("rows,d_ff", [(256, 128), (257, 192 + 64), (510, 384)])
 def test_block_gemm_tile_edges(rows, d_ff):
     shape = W.Shape(256, 2, 4, 64, 64)
