@@ -460,7 +460,11 @@ __global__ __launch_bounds__(TEAMS * 64 * (D / 32 < 4 ? 4 : D / 32)) void gdn_sc
 // d = 128 needs most of the LDS for one.  256 CUs, 1024 rows a unit (us, one
 // team / two): d = 32, 256 units 161 / 131, 272 units 201 / 256, 1024 units
 // 412 / 530; d = 64, 256 units 247 / 209, 272 units 486 / 407, 1024 units
-// 994 / 848.
+// 994 / 848.  Units of one chunk leave a second team idle: whole calls of 48-row
+// units, d = 32, 2 units 24.5 / 28.1, 256 units 37.4 / 40.5; d = 64, 2 units
+// 32.2 / 36.3, 2048 units 370 / 401; of two chunks two teams win (d = 64, 2048
+// units 651 / 613).  The lengths are on the device, so the rule does not see
+// them.
 template <int D>
 hipError_t run_scan(const ScanArgs& a, hipStream_t s) {
   const int64_t units = (int64_t)a.n_seg * a.n_layers * a.H_v;

@@ -891,9 +891,14 @@ hipError_t run(const ScanArgs& a, hipStream_t s) {
   if (units == 0) return hipSuccess;
   // Twice the units on a CU each: two workgroups per unit.  Blocks come in
   // groups of 16, 8 units' halves.  Measured (us, one workgroup per unit /
-  // two): 2048 rows a unit, 64 units 82 / 76, 128 units 83 / 78, 144 units 83 /
-  // 146; 128 rows a unit, 64 units 18.6 / 17.1, 128 units 19.2 / 18.0, 144
-  // units 19.2 / 29.0.
+  // two; d = 128): 2048 rows a unit, 64 units 82 / 76, 128 units 83 / 78, 144
+  // units 83 / 146; 128 rows a unit, 64 units 18.6 / 17.1, 128 units 19.2 / 18.0,
+  // 144 units 19.2 / 29.0.  Narrower heads, whole calls of one layer (d_model
+  // 64): d = 64, 2048 rows, 4 units 79.2 / 77.2, 128 units 111.5 / 110.4, 144
+  // units 115 / 174; d = 32, 4 units 78.2 / 77.7, 64 units 84.2 / 83.3, 128 units
+  // 94.5 / 96.6 (two taken), 144 units 104 / 163; with units of 1 to
+  // 128 rows two are 0 to 4% faster up to 128 units (2% slower at 64 units of 32
+  // rows, d = 32) and 16 to 25% slower at 144.
   if constexpr (!SPLIT) {
     const int64_t halves = (units + 7) / 8 * 16;
     if (halves <= device_cus()) {

@@ -89,7 +89,9 @@ __global__ __launch_bounds__(kTileThreads<TileBig>, 1) void block_gemm_kernel(Bl
     }
   } else {
     // 8 rows of the residual are read before the first of them is written:
-    // read one by one, every row would wait for memory
+    // read one by one, every row would wait for memory.  (With one K-step, K =
+    // 64, the prologue's refetches may still be on their way to the LDS here;
+    // loads return in order, so the wait for these rows covers them.)
     float* out = static_cast<float*>(a.C) + lrow * a.ldc + n0 + wn * 128 + 4 * lc;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {

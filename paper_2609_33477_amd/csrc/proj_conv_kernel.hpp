@@ -10,11 +10,11 @@
 //   k_hat  = k / sqrt(|k|^2 + eps)                           (per key head)
 //   G      = log2 alpha = -exp(A_log) softplus(a + dt_bias) log2(e)
 //   beta   = sigmoid(b)
-// The projection never reaches HBM: each 256 x 256 output tile is finished in
-// registers and only k_hat / v (bf16, head-major [H][T][d]), G and beta ([H_v][T],
+// The projection never reaches HBM: each output tile (256 x 256 or 128 x 128) is
+// finished in registers and only k_hat / v (bf16, head-major [H][T][d]), G and beta ([H_v][T],
 // fp32) and the tail rows are written.
 //
-// Main loop: the 256 x 256 tile of sr_tile.hpp (8 waves of 64 x 128 on
+// Main loop: the tiles of sr_tile.hpp (8 waves of 64 x 128 or 4 of 32 x 128 on
 // v_mfma_f32_16x16x32_bf16, K-steps of 64 through the LDS by DMA).  fp8 (E4M3)
 // weights are staged as bytes and converted to bf16 after the fragment read
 // (exact); the per-channel scale is folded into the conv taps (the conv is
@@ -32,11 +32,12 @@
 // more MFMA work at OLMo's shape, against an unfused projection whose fp32
 // rows went through HBM.
 //
-// Conv epilogue, in registers: M-tiles overlap by 3 rows (stride 253), so
-// every output row's w-1 predecessors are in the tile (the first tile starts
-// at row 0 and outputs all of its rows).  Lane l of wave w holds rows
-// 64 (w / 2) + 16 (l / 16) + 0..15 of 8 columns; the conv runs down those
-// registers (the 3 rows above the lane's first come from the lane before it
+// Conv epilogue, in registers: M-tiles overlap by 3 rows (stride 253 or 125),
+// so every output row's w-1 predecessors are in the tile (the first tile starts
+// at row 0 and outputs all of its rows).  With MI = 4 (2 in the small tile)
+// accumulator blocks of rows and WN = 2 (1) waves along N, lane l of wave w
+// holds rows 16 MI (w / WN) + 4 MI (l / 16) + 0 .. 4 MI - 1 of 8 columns; the
+// conv runs down those registers (the 3 rows above the lane's first come from the lane before it
 // through a small LDS exchange), then SiLU.  The weight rows of a head are fed
 // in the order that gives a lane 4 neighbouring columns of each 64 (2 of a
 // 32-wide head), so 64 columns of a row leave as one 8-byte store per lane
@@ -84,7 +85,6 @@ struct Epi {
   static_assert(GATE_OFF + C::WAVES * GATE_WAVE <= kTileLds<C>, "epilogue areas");
 };
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 
 typedef __attribute__((address_space(3))) float lfloat;
 typedef float nf32x4 __attribute__((ext_vector_type(4)));
@@ -690,7 +690,16 @@ hipError_t run(const ProjConvBatch& b, hipStream_t s) {
   // D = 2048: 153 / 561 62 / 66, 289 / 1089 118 / 103; D = 5120: 99 / 325
   // 112 / 80, 165 / 585 118 / 132, 297 / 1105 229 / 205.
   // So small tiles where one round holds them all, or where the big ones would
-  // leave the last of two or more rounds mostly idle.
+  // leave the last of two or more rounds mostly idle.  Those are kernels of bf16
+  // square heads; for the other forms whole calls were timed with either tile
+  // forced: of 268 shapes (bf16 and fp8; square heads, 96 x 192 ones, and 196 to
+  // 516 columns with up to 120K rows) the rule's choice was within 1% of the
+  // better one at 254 and 5% behind at worst (big / small, us): fp8, 16 key and
+  // 48 value heads of 128: D = 5120, 1024 rows 150 / 164, 4096 rows 463 / 464; D
+  // = 1024, 4096 rows 245 / 240 (big taken); 96 x 192: 30 heads, D = 3840, 1024
+  // rows 136 / 148, 4096 rows 412 / 431; 8 heads, 4 layers, 2048 rows 155 / 148
+  // (big taken, the worst); 196 columns, 20K rows 181 / 159, 120K rows 284 /
+  // 320.
   const int64_t cus = device_cus();
   const int64_t big = (int64_t)b.n_layers * tiles_m(a.T, TileBig::ROWS) * ((a.N + 255) / 256);
   const int64_t small = (int64_t)b.n_layers * tiles_m(a.T, TileSmall::ROWS) * ((a.N + 127) / 128);
